@@ -803,7 +803,8 @@ def main():
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                      "traffic": measured_traffic(launch_cfg),
-                     "kernel": ("k_dslash_lds" if launch_cfg[3] else "k_dslash") + " (half Dslash, FP32)",
+                     "kernel": (("k_dslash_pair" if launch_cfg[0] >= 2 and launch_cfg[1] == 64 and launch_cfg[3] <= 3
+                                 else "k_dslash_lds") if launch_cfg[3] else "k_dslash") + " (half Dslash, FP32)",
                      "launch_config": {"rhs_per_thread": launch_cfg[0], "sites_per_block": launch_cfg[1],
                                        "nontemporal_links": launch_cfg[2], "lds_links": launch_cfg[3],
                                        "xcd_map": launch_cfg[4]},

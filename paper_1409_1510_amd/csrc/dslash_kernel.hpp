@@ -17,6 +17,8 @@
 
 #include "internal.hpp"
 
+#include <type_traits>
+
 namespace dslash {
 
 template <typename Real> struct CT;
@@ -890,6 +892,392 @@ __global__ void __launch_bounds__(64 * WPB, WPB / 4 * (sizeof(LT) > 8 ? 1 : 2)) 
   }
 }
 
+// f(integral_constant 0), ..., f(integral_constant N - 1)
+template <int N, int I = 0, typename F> __device__ __forceinline__ void static_for(F &&f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    static_for<N, I + 1>(f);
+  }
+}
+
+// ---- pair form -------------------------------------------------------------------------------
+// 16 bytes at an address that need only be a multiple of 8 (complex64 vectors)
+typedef float f4a8_t __attribute__((ext_vector_type(4), aligned(8)));
+typedef unsigned u4_t __attribute__((ext_vector_type(4)));
+
+// Link entries of the two sites of a lane (LDS plane-major, sites adjacent).
+template <typename LT> struct LinkPair;
+template <> struct LinkPair<float2> {
+  __device__ static void load(const float2 *p, float (&re)[2], float (&im)[2]) {
+    const float4 v = *reinterpret_cast<const float4 *>(p);
+    re[0] = v.x;
+    im[0] = v.y;
+    re[1] = v.z;
+    im[1] = v.w;
+  }
+};
+template <> struct LinkPair<__half2> {
+  __device__ static void load(const __half2 *p, float (&re)[2], float (&im)[2]) {
+    const uint2 u = *reinterpret_cast<const uint2 *>(p);
+    const float2 a = __half22float2(*reinterpret_cast<const __half2 *>(&u.x));
+    const float2 b = __half22float2(*reinterpret_cast<const __half2 *>(&u.y));
+    re[0] = a.x;
+    im[0] = a.y;
+    re[1] = b.x;
+    im[1] = b.y;
+  }
+};
+
+// LDS of the pair form: as the whole-site form, with the neighbour table per pair of sites.
+constexpr size_t kNbrTablePairBytes = size_t(4) * 32 * sizeof(uint4);
+
+// Waves per SIMD of the pair form: 128 registers and 16 waves per CU (two workgroups of 8 waves with
+// FP32 links, four of 4 with FP16 links), or 256 registers and 8 waves with two rhs per lane, whose
+// gathers do not fit in 128.
+template <typename LT, int RT> constexpr int pair_waves_per_simd(int wpb) {
+  return RT == 2 ? (wpb > 8 ? wpb / 4 : 2) : (wpb == 4 && sizeof(LT) > 4 ? 2 : 4);
+}
+
+// Whole-site LDS form with two neighbouring sites (2 i, 2 i + 1) per lane, for complex64 vectors
+// on lattices with Lx divisible by 4 (a pair never straddles an x row; V/2 is then a multiple of
+// 16).  What bounds the one-site form is the rate at which a CU's vector memory path takes load
+// instructions: a wave's 8-byte loads move 32 bytes per clock, its 16-byte loads 62 (measured on
+// L1-resident data), so a tile's gathers alone cost ~41 us of the 76 us launch at 32^3 x 8 with
+// 16 rhs (FP32).  Here every gather, link staging load and store is 16 bytes wide: 66 us; 58 us of
+// that remain without any arithmetic or link reads, 344 MB past L2 at 5.9 TB/s.
+//   * y, z and t neighbours of a pair are a pair; the eight x neighbours of a pair are all among
+//     the pair itself and the pairs before and after it in its row (three loads, not four), picked
+//     by the parity of the row.
+//   * the two 32-lane halves of a wave take different rhs: lane (pair i, half h) computes rhs
+//     r0 + h RT + r of a tile of 2 RT; the rhs offset is in the buffer loads' vector offset, so a
+//     rhs past n reads past the buffer's range (returns 0) and is not stored.
+// Same hop order and FMA sequence per site and rhs as k_dslash, and the same tree over the 64
+// sites of a block for the fused <p, Mp> partials (bit-identical outputs).
+template <typename LT, int RT, int NR, bool EPI, int WPB, bool NT>
+__global__ void __launch_bounds__(64 * WPB, (pair_waves_per_simd<LT, RT>(WPB))) k_dslash_pair(Args a) {
+  using C = float2;
+  constexpr int PL = lds_staged_planes(NR);
+  constexpr int SPL = 16 / int(sizeof(LT));  // sites per lane, and planes per wave, of a staging load
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  LT *sl = reinterpret_cast<LT *>(smem_raw);
+  const Geometry &g = a.g;
+  int sblk;
+  if (!lds_block(a, sblk)) return;  // uniform for the whole workgroup
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int pi = lane & 31, h = lane >> 5;
+  const unsigned vh = g.vh;
+  const unsigned s0 = unsigned(sblk) * 64;
+  const LT *__restrict__ links = static_cast<const LT *>(a.links);
+  const unsigned plane_bytes = vh * unsigned(sizeof(C));
+  // neighbour table of the 32 pairs, byte offsets within a colour plane: [0] the pair before, the
+  // pair itself, the pair after in its x row, and the row's parity; [mu] the pairs at +1, -1, +3, -3
+  uint4 *nbt = reinterpret_cast<uint4 *>(smem_raw + lds_nbr_offset<float, LT, NR>());
+  // ---- gathers of one tile: LOOK hops ahead of the arithmetic (the compiler alone keeps one hop in
+  // flight).  Hop i = 4 (mu - 1) + k of the y, z and t directions is held in slot i % (LOOK + 1).
+  constexpr int LOOK = EPI ? 2 : 3;
+  v4u_t v[LOOK + 1][RT][3], xm[RT][3], xc[RT][3], xp[RT][3];
+  uint4 nb;
+  bool odd;
+  int pj = pi;
+  __amdgpu_buffer_rsrc_t rs;
+  const unsigned hoff = unsigned(h * RT * 3) * plane_bytes;
+  auto gather = [&](unsigned off, int r, int b) -> v4u_t {
+    return __builtin_amdgcn_raw_buffer_load_b128(rs, off + hoff + unsigned(r * 3) * plane_bytes,
+                                                 unsigned(b) * plane_bytes, 0);
+  };
+  auto issue = [&](auto ic) {
+    constexpr int i = decltype(ic)::value;
+    if constexpr (i % 4 == 0) nb = nbt[(1 + i / 4) * 32 + pj];
+    const unsigned off = (i & 3) == 0 ? nb.x : ((i & 3) == 1 ? nb.y : ((i & 3) == 2 ? nb.z : nb.w));
+#pragma unroll
+    for (int r = 0; r < RT; ++r)
+#pragma unroll
+      for (int b = 0; b < 3; ++b) v[i % (LOOK + 1)][r][b] = gather(off, r, b);
+  };
+  // the x pairs and the first LOOK hops of a tile; its buffer covers the rhs that exist (past the
+  // last tile none: the loads read nothing and return 0)
+  auto start_tile = [&](int tile) {
+    const int r0 = min(tile * 2 * RT, a.n);
+    const char *in = static_cast<const char *>(a.in) + size_t(r0) * 3 * plane_bytes;
+    rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(in), short(0),
+                                           int(unsigned(min(2 * RT, a.n - r0)) * 3u * plane_bytes), kBufWord3);
+    const uint4 nx = nbt[pj];
+    odd = nx.w != 0;
+#pragma unroll
+    for (int r = 0; r < RT; ++r)
+#pragma unroll
+      for (int b = 0; b < 3; ++b) {
+        xm[r][b] = gather(nx.x, r, b);
+        xc[r][b] = gather(nx.y, r, b);
+        xp[r][b] = gather(nx.z, r, b);
+      }
+    static_for<LOOK>([&](auto ic) { issue(ic); });
+  };
+  // the active rhs of a tile, one bit each (uniform: scalar loads)
+  auto tile_mask = [&](int tile) -> unsigned {
+    unsigned m = 0;
+#pragma unroll
+    for (int k = 0; k < 2 * RT; ++k) {
+      const int q = tile * 2 * RT + k;
+      if (q < a.n && (!a.active || a.active[q])) m |= 1u << k;
+    }
+    return m;
+  };
+  // first tile from `tile` on with an active rhs (its rhs in `mask`); the tiles passed over get zero
+  // partials
+  unsigned mask = 0;
+  auto next_tile = [&](int tile) -> int {
+    for (; tile < a.ntiles; tile += WPB) {
+      mask = tile_mask(tile);
+      if (mask) break;
+      if constexpr (EPI) {
+        if (a.partial && lane < 2 * RT && tile * 2 * RT + lane < a.n)
+          a.partial[size_t(tile * 2 * RT + lane) * ((vh + 63) / 64) + sblk] = 0.0;
+      }
+    }
+    return tile;
+  };
+
+  // ---- set-up: link loads first, then the neighbour table and the first tile's gathers behind them,
+  // so that their latencies overlap; a wave load covers SPL planes, 16 bytes a lane
+  int tile;
+  {
+    constexpr int NI = (PL + SPL - 1) / SPL;   // wave loads
+    constexpr int PW = (NI + WPB - 1) / WPB;   // of them per wave
+    constexpr int CH = PW <= 9 ? PW : 9;       // in flight before any is written to LDS
+    constexpr int LPP = 64 / SPL;              // lanes per plane
+    constexpr bool whole = PL % (SPL * WPB * CH) == 0;
+    const int pp = lane / LPP, st = (lane % LPP) * SPL;
+    const unsigned ls = s0 + st < vh ? s0 + st : 0u;  // a lane past the last site stages site 0's links
+    u4_t w[CH];
+    auto fetch = [&](int c0) {
+#pragma unroll
+      for (int i = 0; i < CH; ++i) {
+        const int pl = (wave + (c0 + i) * WPB) * SPL + pp;
+        if (whole || (c0 + i < PW && pl < PL)) {
+          const u4_t *q = reinterpret_cast<const u4_t *>(links + size_t(pl) * vh + ls);
+          if constexpr (NT) w[i] = __builtin_nontemporal_load(q);
+          else w[i] = *q;
+        }
+      }
+    };
+    auto stash = [&](int c0) {
+#pragma unroll
+      for (int i = 0; i < CH; ++i) {
+        const int pl = (wave + (c0 + i) * WPB) * SPL + pp;
+        if (whole || (c0 + i < PW && pl < PL)) *reinterpret_cast<u4_t *>(sl + pl * 64 + st) = w[i];
+      }
+    };
+    fetch(0);
+    if (wave < 4) {  // wave mu: two offsets per half
+      const int mu = wave;
+      const unsigned sp = s0 + 2 * pi < vh ? s0 + 2 * pi : 0u;  // first site of the pair (0 past the end)
+      const unsigned q1 = fast_div(sp, a.div_xh);
+      const unsigned q2 = fast_div(q1, a.div_y);
+      const unsigned q3 = fast_div(q2, a.div_z);
+      const int xh = int(sp - q1 * unsigned(g.lxh));
+      const int y = int(q1 - q2 * unsigned(g.ly));
+      const int z = int(q2 - q3 * unsigned(g.lz));
+      const int t = int(q3);
+      const unsigned rowbase = sp - unsigned(xh);
+      uint2 n;
+      if (mu == 0) {
+        n.x = h ? (rowbase + unsigned(xh + 2 >= g.lxh ? 0 : xh + 2)) * 8u
+                : (rowbase + unsigned(xh == 0 ? g.lxh - 2 : xh - 2)) * 8u;
+        n.y = h ? unsigned((y + z + t + a.out_parity) & 1) : sp * 8u;
+      } else {
+        const int d = h ? 3 : 1;
+        n.x = hop_site(g, mu, d, sp, rowbase, 0, y, z, t) * 8u;
+        n.y = hop_site(g, mu, -d, sp, rowbase, 0, y, z, t) * 8u;
+      }
+      reinterpret_cast<uint2 *>(nbt)[(mu * 32 + pi) * 2 + h] = n;
+    }
+    __syncthreads();
+    tile = next_tile(wave);
+    if constexpr (PW > CH) {
+#pragma unroll 1
+      for (int c0 = 0; c0 + CH < PW; c0 += CH) {
+        stash(c0);
+        fetch(c0 + CH);
+      }
+    }
+    start_tile(tile);  // also without a tile: a branch here would make the waits below cover the gathers
+    stash((PW - 1) / CH * CH);
+  }
+  // compressed Naik links: rebuilt once per site, as in the one-site form
+  C *row2 = reinterpret_cast<C *>(sl + PL * 64);
+  if constexpr (NR == 9) {
+    for (int item = threadIdx.x; item < 8 * 64; item += 64 * WPB) {
+      const int k = item >> 6, ln = item & 63;
+      const unsigned site = s0 + ln;
+      Lnk<float> Lk;
+      load_naik<float, LT, NR, NT>(links, 8 + k, vh, site < vh ? site : 0u, Lk);
+#pragma unroll
+      for (int e = 0; e < 9; ++e) row2[(k * 9 + e) * 64 + ln] = make_float2(Lk.re[e / 3][e % 3], Lk.im[e / 3][e % 3]);
+    }
+  }
+  __syncthreads();
+  if constexpr (NR == 14 || NR == 13) {
+    for (int item = threadIdx.x; item < 8 * 64; item += 64 * WPB) {
+      const int k = item >> 6, ln = item & 63;
+      Lnk<float> Lk;
+      load_naik<float, LT, NR, false>(sl, 8 + k, 64u, unsigned(ln), Lk);
+#pragma unroll
+      for (int b = 0; b < 3; ++b) row2[(k * 3 + b) * 64 + ln] = make_float2(Lk.re[2][b], Lk.im[2][b]);
+    }
+    __syncthreads();
+  }
+
+  // entry (ra, b) of the link of hop k (0..15) for the two sites
+  auto link_entry = [&](int k, int ra, int b, float (&re)[2], float (&im)[2]) {
+    if constexpr (NR == 9) {
+      if (k >= 8) {
+        LinkPair<float2>::load(row2 + 2 * pj + ((k - 8) * 9 + ra * 3 + b) * 64, re, im);
+        return;
+      }
+    } else if constexpr (NR != 18) {
+      if (k >= 8 && ra == 2) {
+        LinkPair<float2>::load(row2 + 2 * pj + ((k - 8) * 3 + b) * 64, re, im);
+        return;
+      }
+    }
+    LinkPair<LT>::load(sl + 2 * pj + (link_plane(k, NR) + ra * 3 + b) * 64, re, im);
+  };
+  while (tile < a.ntiles) {
+    const int q0 = tile * 2 * RT + h * RT;  // this lane's first rhs
+    float acc_re[RT][2][3], acc_im[RT][2][3];
+#pragma unroll
+    for (int r = 0; r < RT; ++r)
+#pragma unroll
+      for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) acc_re[r][s][c] = acc_im[r][s][c] = 0.f;
+    // The arithmetic of a hop ends here for the scheduler, and the link reads of the next one start
+    // (left to itself the compiler issues the LDS reads of all 16 hops at once and spills them).
+    auto fence = [&] {
+#pragma unroll
+      for (int r = 0; r < RT; ++r)
+        asm volatile("" : "+v"(acc_re[r][0][0]), "+v"(acc_re[r][0][1]), "+v"(acc_re[r][0][2]), "+v"(acc_im[r][0][0]),
+                     "+v"(acc_im[r][0][1]), "+v"(acc_im[r][0][2]), "+v"(acc_re[r][1][0]), "+v"(acc_re[r][1][1]),
+                     "+v"(acc_re[r][1][2]), "+v"(acc_im[r][1][0]), "+v"(acc_im[r][1][1]), "+v"(acc_im[r][1][2]),
+                     "+v"(pj));
+    };
+    // acc += sign * L x, x[r][b] = the pair's (re, im, re, im) (hops +1, -1, +3, -3 are k / 4 = 0 .. 3)
+    auto hop = [&](auto kc, const v4u_t (&x)[RT][3]) {
+      constexpr int k = decltype(kc)::value;
+      constexpr bool neg = (k / 4) & 1;
+#pragma unroll
+      for (int ra = 0; ra < 3; ++ra) {
+#pragma unroll
+        for (int b = 0; b < 3; ++b) {
+          float lre[2], lim[2];
+          link_entry(k, ra, b, lre, lim);
+#pragma unroll
+          for (int s = 0; s < 2; ++s) {
+            const float lr = neg ? -lre[s] : lre[s];
+            const float li = neg ? -lim[s] : lim[s];
+#pragma unroll
+            for (int r = 0; r < RT; ++r) {
+              const float vx = __uint_as_float(x[r][b][2 * s]), vy = __uint_as_float(x[r][b][2 * s + 1]);
+              acc_re[r][s][ra] = fmaf(lr, vx, acc_re[r][s][ra]);
+              acc_re[r][s][ra] = fmaf(-li, vy, acc_re[r][s][ra]);
+              acc_im[r][s][ra] = fmaf(lr, vy, acc_im[r][s][ra]);
+              acc_im[r][s][ra] = fmaf(li, vx, acc_im[r][s][ra]);
+            }
+          }
+        }
+      }
+      fence();
+    };
+    fence();
+    static_for<4>([&](auto kc) {  // x direction: +1, -1, +3, -3 from shifts of the row by -2..2 sites
+      constexpr int k = decltype(kc)::value;
+      v4u_t x[RT][3];
+#pragma unroll
+      for (int r = 0; r < RT; ++r)
+#pragma unroll
+        for (int b = 0; b < 3; ++b) {
+          const v4u_t M = xm[r][b], Z = xc[r][b], P = xp[r][b];
+          const v4u_t lo = {M[2], M[3], Z[0], Z[1]}, hi = {Z[2], Z[3], P[0], P[1]};  // shifts -1, +1
+          const v4u_t u = k == 0 ? hi : (k == 1 ? Z : (k == 2 ? P : lo));  // rows of odd parity
+          const v4u_t w = k == 0 ? Z : (k == 1 ? lo : (k == 2 ? hi : M));  // rows of even parity
+#pragma unroll
+          for (int e = 0; e < 4; ++e) x[r][b][e] = odd ? u[e] : w[e];
+        }
+      hop(std::integral_constant<int, 4 * k>{}, x);
+    });
+    const bool valid = s0 + 2 * pi < vh;
+    bool act[RT];
+#pragma unroll
+    for (int r = 0; r < RT; ++r) act[r] = valid && ((mask >> (h * RT + r)) & 1u);
+    const size_t tile_off = size_t(q0) * 3 * vh + s0 + 2 * pi;  // the lane's first output
+    f4a8_t pv[RT][3];
+    static_for<12>([&](auto ic) {
+      constexpr int i = decltype(ic)::value;
+      if constexpr (i + LOOK < 12) issue(std::integral_constant<int, i + LOOK>{});
+      if constexpr (EPI && i + LOOK == 12) {
+        const C *p = static_cast<const C *>(a.pvec) + tile_off;
+#pragma unroll
+        for (int r = 0; r < RT; ++r)
+          if (act[r]) {
+#pragma unroll
+            for (int c = 0; c < 3; ++c) pv[r][c] = *reinterpret_cast<const f4a8_t *>(p + size_t(r * 3 + c) * vh);
+          }
+      }
+      hop(std::integral_constant<int, 4 * (i & 3) + 1 + i / 4>{}, v[i % (LOOK + 1)]);
+    });
+    const int done = tile;
+    tile = next_tile(tile + WPB);
+    if (tile < a.ntiles) start_tile(tile);
+    C *out = static_cast<C *>(a.out) + tile_off;
+    if constexpr (!EPI) {
+#pragma unroll
+      for (int r = 0; r < RT; ++r) {
+        if (!act[r]) continue;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          const f4a8_t o = {acc_re[r][0][c], acc_im[r][0][c], acc_re[r][1][c], acc_im[r][1][c]};
+          *reinterpret_cast<f4a8_t *>(out + size_t(r * 3 + c) * vh) = o;
+        }
+      }
+    } else {
+      const float m2 = float(a.mass2);
+      const unsigned nw = (vh + 63) / 64;
+#pragma unroll
+      for (int r = 0; r < RT; ++r) {
+        double d0 = 0.0, d1 = 0.0;
+        if (act[r]) {
+#pragma unroll
+          for (int c = 0; c < 3; ++c) {
+            const f4a8_t p = pv[r][c];
+            f4a8_t o;
+            o.x = fmaf(m2, p.x, -acc_re[r][0][c]);
+            o.y = fmaf(m2, p.y, -acc_im[r][0][c]);
+            o.z = fmaf(m2, p.z, -acc_re[r][1][c]);
+            o.w = fmaf(m2, p.w, -acc_im[r][1][c]);
+            *reinterpret_cast<f4a8_t *>(out + size_t(r * 3 + c) * vh) = o;
+            d0 = fma(double(p.x), double(o.x), d0);
+            d0 = fma(double(p.y), double(o.y), d0);
+            d1 = fma(double(p.z), double(o.z), d1);
+            d1 = fma(double(p.w), double(o.w), d1);
+          }
+        }
+        if (a.partial) {
+          // the one-site form's tree: site s + site (s + 32), ..., s + (s + 2), then site 0 + site 1
+#pragma unroll
+          for (int off = 16; off > 0; off >>= 1) {
+            d0 += __shfl_down(d0, off, 64);
+            d1 += __shfl_down(d1, off, 64);
+          }
+          if (pi == 0 && done * 2 * RT + h * RT + r < a.n)
+            a.partial[size_t(done * 2 * RT + h * RT + r) * nw + sblk] = d0 + d1;
+        }
+      }
+    }
+  }
+}
+
 // 32-site LDS form (plain half Dslash): a workgroup of 32 sites x WPB waves stages half the links
 // of the whole-site form, so that an FP64 workgroup (74 KB) shares a CU with another (and an
 // FP32 or FP16 one with three).  The two 32-lane halves of a wave take different rhs: lane
@@ -1206,6 +1594,13 @@ void launch_t(const Args &a, dim3 grid, hipStream_t st) {
 
 template <typename Real, typename LT, int RT, int NR, bool EPI, int WPB, bool NT>
 void launch_lds(const Args &a, dim3 grid, hipStream_t st) {
+  if constexpr (sizeof(Real) == 4 && RT >= 2) {
+    if (a.g.lx % 4 == 0) {
+      k_dslash_pair<LT, RT / 2, NR, EPI, WPB, NT>
+          <<<grid, 64 * WPB, lds_nbr_offset<float, LT, NR>() + kNbrTablePairBytes, st>>>(a);
+      return;
+    }
+  }
   constexpr size_t lds = lds_nbr_offset<Real, LT, NR>() + kNbrTableBytes;
   k_dslash_lds<Real, LT, RT, NR, EPI, WPB, NT><<<grid, 64 * WPB, lds, st>>>(a);
 }

@@ -535,3 +535,42 @@ def test_register_tile_offsets_fit_32_bits_on_large_lattices():
             rt = hisq.hisq_get_launch(lat.ctx, prec, n, 1)[0]
             assert 3 * rt * lat.vh < 2 ** 32
     lat.close()
+
+
+# ---- two sites per lane (16-byte gathers): lattices with Lx divisible by 4, FP32 and FP16 links ------
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dims", [(4, 4, 4, 4), (4, 6, 4, 10), (8, 4, 6, 4), (12, 4, 4, 6), (20, 6, 4, 4),
+                                  (32, 8, 4, 4)])
+@pytest.mark.parametrize("recon", [18, 14, 13, 9])
+def test_pair_form_is_bit_identical(dims, recon):
+    """The LDS form with two sites per lane against the register-tile form, bit for bit: rows of 2
+    sites (both x neighbours wrap) up to 16, a partial last block of 64 sites, rhs counts below,
+    at and above a tile, vectors aligned to 8 bytes only, and the fused M form's <p, Mp>."""
+    lat, _, _ = make_lattice(dims, 77, recon=recon)
+    vh = lat.vh
+    g = torch.Generator(device=DEV)
+    g.manual_seed(5)
+    for prec in (hisq.HISQ_F32, hisq.HISQ_F16):
+        for n in (1, 2, 3, 4, 5, 9, 17):
+            flat = torch.randn(2 * n * 3 * vh + 2, generator=g, dtype=torch.float32, device=DEV)
+            v = torch.view_as_complex(flat[2:].view(-1, 2)).view(n, 3, vh)  # 8 bytes past a 16-byte boundary
+            assert v.data_ptr() % 16 == 8
+            ref = {}
+            for cfg in [(1, 64, 0, 0, 0)] + [(rt, 64, nt, lds, 0) for rt in (2, 4) for nt in (0, 1)
+                                             for lds in (1, 2, 3) if not (rt == 4 and lds == 3)]:
+                hisq.hisq_set_launch(lat.ctx, prec, n, cfg)
+                buf = torch.zeros(2 * n * 3 * vh + 2, dtype=torch.float32, device=DEV)
+                out = torch.view_as_complex(buf[2:].view(-1, 2)).view(n, 3, vh)
+                got = []
+                for par in (1, 0):
+                    lat.dslash(par, prec, v, out)
+                    got.append(out.clone())
+                q, pq = lat.apply_m(prec, 0.3, v, out, with_pq=True)
+                got += [q.clone(), pq]
+                if not ref:
+                    ref = got
+                for a, b in zip(got, ref):
+                    assert torch.equal(torch.view_as_real(a) if a.is_complex() else a,
+                                       torch.view_as_real(b) if b.is_complex() else b), (cfg, prec, n)
+    lat.close()
