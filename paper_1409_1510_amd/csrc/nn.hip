@@ -15,6 +15,7 @@
 //
 // Parameters (complex, canonical order): W_in[C]; for l = 1..L: (W_l[C][C] [out][in] if l >= 2),
 // a_l[9][C]; W_out[C].  Hop h: 0 self, 1+mu forward, 5+mu backward.
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -228,6 +229,216 @@ k_nn_stencil(NNArgs A, const AT *__restrict__ in, AT *__restrict__ out, const fl
   }
 #pragma unroll
   for (int col = 0; col < 3; ++col) Act<AT>::store(ob + (size_t(col) * V + X) * NR, acc[col]);
+}
+
+typedef short bf16x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// ---- training stencil on matrix cores -------------------------------------------------------
+// out = S(a, in) or S^dag(a, in) for BF16 activations and FP16 links, and with WG (adjoint only) the
+// stencil-weight gradient from the same link products: with t_h = the hop h of the adjoint applied to
+// g = in, sum_x conj((H_k phi)(x)) g(x) = sum_x conj(phi(x)) (H_k^dag g)(x) and H_k^dag g = t_h for
+// the hop h opposite to k, so the gradient needs phi only at the site itself.
+//
+// A wave takes 16 sites; lane (site l / 4, q = l % 4) holds channels 2q and 2q + 1.  The 3 x 3 link
+// product of a hop is v_mfma_f32_4x4x4_16b_bf16 (one 4 x 4 block per site: row = colour, column =
+// lane's channel, contraction over (re, im) of the neighbour's colours).  An FP16 link entry (11
+// significant bits) is the exact sum of two BF16 numbers (8 bits each) and activations are BF16, so
+// every product is exact and the accumulation FP32, as with FP32 arithmetic on the FP16 links: three
+// instructions contract (high u0, u1), (high u2, low u2), (low u0, u1).  What bounds the one-thread-
+// per-site kernel is the FP32 arithmetic of the products (1152 of ~1600 cycles per hop and 64 sites);
+// here they take 384 on the matrix cores beside the rest.  The split links of a site (48 registers)
+// serve all samples of the wave; the gradient sums stay in FP64 registers over all sites of a wave.
+// Figures: at stencil_mfma below.
+struct StencilArgs {
+  Geometry g;
+  const __half2 *links[2];
+  const bf16 *in, *phi;   // phi: activations the weight gradient is taken against (WG)
+  bf16 *out;
+  const float2 *a;
+  double *partial;        // WG: [workgroup][9][C][re, im]
+  size_t sample_stride;
+  int batch, spw;         // samples, samples per work item
+  int nsg, nitem;         // 16-site groups, work items (site group, sample group) of an XCD
+};
+
+template <bool ADJ, bool WG>
+__global__ void __launch_bounds__(kThreads, 2) k_nn_stencil_mfma(StencilArgs A) {
+  typedef unsigned u2v __attribute__((__vector_size__(8)));
+  const Geometry &g = A.g;
+  const unsigned V = 2u * g.vh;
+  const int lane = threadIdx.x & 63;
+  const int q = lane & 3;
+  const int row = q < 2 ? q : 2;  // colour row of the A operand (row 3 is not used)
+  // Workgroups are dealt round-robin to the 8 XCDs: XCD x takes the x-th eighth of the site groups
+  // (of each sample group), so that the neighbours its waves read are mostly in its own L2
+  const int xcd = blockIdx.x & 7;
+  const int wave = __builtin_amdgcn_readfirstlane((blockIdx.x >> 3) * (kThreads / 64) + (threadIdx.x >> 6));
+  const int nwaves = (gridDim.x >> 3) * (kThreads / 64);  // of this XCD
+  const int per = (A.nsg + 7) / 8;                        // site groups of this XCD
+  constexpr int LOOK = WG ? 2 : 4;
+  __shared__ float4 cf[9 * 4];  // [hop][channel / 2]: coefficients of two channels
+  if (threadIdx.x < 36) {
+    const int h = threadIdx.x >> 2, c = 2 * (threadIdx.x & 3);
+    const float2 c0 = coef<ADJ>(A.a, h, c), c1 = coef<ADJ>(A.a, h, c + 1);
+    cf[threadIdx.x] = make_float4(c0.x, c0.y, c1.x, c1.y);
+  }
+  __syncthreads();
+  double G[9][2][2];
+  if constexpr (WG) {
+#pragma unroll
+    for (int h = 0; h < 9; ++h) G[h][0][0] = G[h][0][1] = G[h][1][0] = G[h][1][1] = 0.0;
+  }
+  const unsigned cs = V * 32u;  // bytes of a colour of one sample
+  auto rsrc = [&](const bf16 *p, int b, int col) {
+    const char *c = reinterpret_cast<const char *>(p + size_t(b) * A.sample_stride) + size_t(col) * cs;
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(c), short(0), int(cs), 0x00020000);
+  };
+  auto load = [](__amdgpu_buffer_rsrc_t r, unsigned off) -> u2v {
+    return __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0);
+  };
+  auto op = [](unsigned lo, unsigned hi) { return __builtin_bit_cast(bf16x4, make_uint2(lo, hi)); };
+  for (int item = wave; item < A.nitem; item += nwaves) {
+    const int sg = xcd * per + item % per;  // uniform; past the last group: lanes without a site
+    const int b0 = (item / per) * A.spw, b1 = min(b0 + A.spw, A.batch);
+    const unsigned X0 = unsigned(sg) * 16 + (lane >> 2);
+    const bool valid = X0 < V;
+    const Site st = decode(g, valid ? X0 : 0u);
+    const unsigned X = valid ? X0 : 0u;
+    unsigned nb[8];
+    unsigned u[8][6];  // split link rows, (re, im) words: high parts 0-2, low parts 3-5
+    const __half2 *lk = st.p ? A.links[1] : A.links[0];
+#pragma unroll
+    for (int h = 0; h < 8; ++h) {
+      nb[h] = nbr1(g, st, h & 3, h < 4 ? 1 : -1) * 32u + unsigned(q) * 8u;
+      const int plane = link_plane(h, 18) + 3 * row;  // fat forward 0..3, backward 4..7
+#pragma unroll
+      for (int j = 0; j < 3; ++j) {
+        const float2 f = __half22float2(lk[size_t(plane + j) * g.vh + st.s]);
+        const unsigned hi = pack_bf(f.x, f.y);
+        u[h][j] = hi;
+        u[h][3 + j] = pack_bf(f.x - __uint_as_float(hi << 16), f.y - __uint_as_float(hi & 0xffff0000u));
+      }
+    }
+    const unsigned self = X * 32u + unsigned(q) * 8u;
+    // the loads run LOOK hops ahead, into the next sample too
+    u2v ws[3], wf[3], w[8][3];
+    auto load_self = [&](int b) {
+#pragma unroll
+      for (int i = 0; i < 3; ++i) {
+        ws[i] = load(rsrc(A.in, b, i), self);
+        if constexpr (WG) wf[i] = load(rsrc(A.phi, b, i), self);
+      }
+    };
+    auto load_hop = [&](int b, int h) {
+#pragma unroll
+      for (int j = 0; j < 3; ++j) w[h][j] = load(rsrc(A.in, b, j), nb[h]);
+    };
+    load_self(b0);
+#pragma unroll
+    for (int h = 0; h < LOOK; ++h) load_hop(b0, h);
+#pragma unroll 1
+    for (int b = b0; b < b1; ++b) {
+      const int bn = b + 1 < b1 ? b + 1 : b;
+      int qq = q;  // (opaque per sample: the coefficients stay in LDS)
+      asm volatile("" : "+v"(qq));
+      float acc[3][2][2];  // [colour][channel][re, im]
+      double ph[3][2][2];
+      {
+        const float4 c = cf[qq];
+        const float cr[2] = {c.x, c.z}, ci[2] = {c.y, c.w};
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+#pragma unroll
+          for (int e = 0; e < 2; ++e) {
+            const float vr = __uint_as_float(ws[i][e] << 16), vi = __uint_as_float(ws[i][e] & 0xffff0000u);
+            acc[i][e][0] = cr[e] * vr - ci[e] * vi;
+            acc[i][e][1] = cr[e] * vi + ci[e] * vr;
+            if constexpr (WG) {
+              const unsigned fe = valid ? wf[i][e] : 0u;  // lanes past the last site add nothing
+              ph[i][e][0] = double(__uint_as_float(fe << 16));
+              ph[i][e][1] = double(__uint_as_float(fe & 0xffff0000u));
+              G[0][e][0] = fma(ph[i][e][0], double(vr), fma(ph[i][e][1], double(vi), G[0][e][0]));
+              G[0][e][1] = fma(ph[i][e][0], double(vi), fma(-ph[i][e][1], double(vr), G[0][e][1]));
+            }
+          }
+        }
+      }
+#pragma unroll
+      for (int h = 0; h < 8; ++h) {
+        if (h + LOOK == 8) load_self(bn);
+        if (h + LOOK < 8) load_hop(b, h + LOOK);
+        else load_hop(bn, h + LOOK - 8);
+        // (the fence: what follows starts after the previous hop's arithmetic, so the operands of one
+        // hop, formed here per sample, are live at a time)
+        asm volatile(""
+                     : "+v"(u[h][0]), "+v"(u[h][1]), "+v"(u[h][2]), "+v"(u[h][3]), "+v"(u[h][4]), "+v"(u[h][5]),
+                       "+v"(acc[0][0][0]), "+v"(acc[0][0][1]), "+v"(acc[0][1][0]), "+v"(acc[0][1][1]),
+                       "+v"(acc[1][0][0]), "+v"(acc[1][0][1]), "+v"(acc[1][1][0]), "+v"(acc[1][1][1]),
+                       "+v"(acc[2][0][0]), "+v"(acc[2][0][1]), "+v"(acc[2][1][0]), "+v"(acc[2][1][1]));
+        if constexpr (WG) {
+          const int k = h == 0 ? 0 : 1 + (h - 1 < 4 ? h + 3 : h - 5);  // the sums the previous hop added to
+          asm volatile("" : "+v"(G[k][0][0]), "+v"(G[k][0][1]), "+v"(G[k][1][0]), "+v"(G[k][1][1]));
+        }
+        const float4 c = cf[(1 + h) * 4 + qq];
+        const float cr[2] = {c.x, c.z}, ci[2] = {c.y, c.w};
+        // the (re, -im) and (im, re) words
+        unsigned ar[6], ai[6];
+#pragma unroll
+        for (int j = 0; j < 6; ++j) {
+          ar[j] = u[h][j] ^ 0x80000000u;
+          ai[j] = (u[h][j] >> 16) | (u[h][j] << 16);
+        }
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          const bf16x4 v01 = op(w[h][0][e], w[h][1][e]), v22 = op(w[h][2][e], w[h][2][e]);
+          f32x4 tr = {0.f, 0.f, 0.f, 0.f}, ti = {0.f, 0.f, 0.f, 0.f};
+          tr = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(op(ar[0], ar[1]), v01, tr, 0, 0, 0);
+          ti = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(op(ai[0], ai[1]), v01, ti, 0, 0, 0);
+          tr = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(op(ar[2], ar[5]), v22, tr, 0, 0, 0);
+          ti = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(op(ai[2], ai[5]), v22, ti, 0, 0, 0);
+          tr = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(op(ar[3], ar[4]), v01, tr, 0, 0, 0);
+          ti = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(op(ai[3], ai[4]), v01, ti, 0, 0, 0);
+#pragma unroll
+          for (int i = 0; i < 3; ++i) {
+            acc[i][e][0] = fmaf(cr[e], tr[i], fmaf(-ci[e], ti[i], acc[i][e][0]));
+            acc[i][e][1] = fmaf(cr[e], ti[i], fmaf(ci[e], tr[i], acc[i][e][1]));
+            if constexpr (WG) {
+              const int k = 1 + (h < 4 ? h + 4 : h - 4);  // the opposite hop
+              const double dr = double(tr[i]), di = double(ti[i]);
+              G[k][e][0] = fma(ph[i][e][0], dr, fma(ph[i][e][1], di, G[k][e][0]));
+              G[k][e][1] = fma(ph[i][e][0], di, fma(-ph[i][e][1], dr, G[k][e][1]));
+            }
+          }
+        }
+      }
+      if (valid) {
+        char *ob = reinterpret_cast<char *>(A.out + size_t(b) * A.sample_stride) + self;
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+          *reinterpret_cast<uint2 *>(ob + i * size_t(cs)) =
+              make_uint2(pack_bf(acc[i][0][0], acc[i][0][1]), pack_bf(acc[i][1][0], acc[i][1][1]));
+      }
+    }
+  }
+  if constexpr (WG) {
+    __shared__ double red[kThreads / 64][9 * NR];
+#pragma unroll
+    for (int h = 0; h < 9; ++h)
+#pragma unroll
+      for (int e = 0; e < 2; ++e)
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+          double v = G[h][e][c];
+#pragma unroll
+          for (int off = 32; off >= 4; off >>= 1) v += __shfl_down(v, off, 64);
+          if (lane < 4) red[threadIdx.x >> 6][(h * NC + 2 * q + e) * 2 + c] = v;
+        }
+    __syncthreads();
+    if (threadIdx.x < 9 * NR)
+      A.partial[size_t(blockIdx.x) * 9 * NR + threadIdx.x] =
+          ((red[0][threadIdx.x] + red[1][threadIdx.x]) + red[2][threadIdx.x]) + red[3][threadIdx.x];
+  }
 }
 
 // ---- fused inference layer -----------------------------------------------------------------
@@ -515,9 +726,6 @@ k_nn_mix_fma(const AT *__restrict__ in, AT *__restrict__ out, size_t ncols, cons
   }
   Act<AT>::store(out + col * NR, o);
 }
-
-typedef short bf16x4 __attribute__((ext_vector_type(4)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // out[col] = M in[col] with v_mfma_f32_16x16x16_bf16: per instruction a wave multiplies the
 // 16 x 16 real mixing matrix (A operand) by 16 columns (B operand).  Operand layout for wave64:
@@ -938,9 +1146,61 @@ int check_nn(hisq_ctx *ctx, const char *fn) {
 
 // ---- kernel launch helpers ----
 
+// Samples a wave of the matrix-core stencil takes at its 16 sites: all of the batch, or fewer on small
+// lattices, so that there are ~8192 waves' worth of work.
+int stencil_spw(const hisq_ctx *ctx, int batch) {
+  const int nsg = int((2u * unsigned(ctx->g.vh) + 15) / 16);
+  const int want = 8192;
+  const int groups = std::min((want + nsg - 1) / nsg, batch);
+  return (batch + groups - 1) / groups;
+}
+
+// Where the matrix-core stencil runs: BF16 activations with FP16 links, and 32-bit byte offsets within
+// a colour.  Splitting a site's links costs ~600 instructions that the samples of a wave share.
+// Measured at 32^3 x 8 with 16 samples: 0.43 ms per launch with all 16 samples per wave, 0.45 with 8,
+// 0.48 with 4 and 0.56 with 2, against 0.54 of k_nn_stencil, so the plain stencil takes it from 4 on;
+// with the weight gradient 0.65, 0.71, 0.80 and 0.99 ms against 1.93 of k_nn_stencil and
+// k_nn_stencil_wgrad, so that form always does.  (Two samples per wave in 16-byte loads, four channels
+// per lane, and a z-outermost site order: 0.43-0.45 ms; three or four waves per SIMD, with spills:
+// 0.44-0.53 ms.)
+bool stencil_mfma(const hisq_ctx *ctx, int prec, int batch, bool wgrad) {
+  return ctx->nn->bf16 && prec == HISQ_F16 && 2u * unsigned(ctx->g.vh) < (1u << 27) &&
+         (wgrad || stencil_spw(ctx, batch) >= 4);
+}
+
+// phi, partial: also the weight-gradient partials against phi (adjoint only); returns the number of
+// workgroups, or a negative error code.
+int launch_stencil_mfma(hisq_ctx *ctx, const NNArgs &N, const void *in, void *out, const float2 *a, bool adj,
+                        const void *phi, double *partial) {
+  StencilArgs A{};
+  A.g = ctx->g;
+  A.links[0] = static_cast<const __half2 *>(N.links[0]);
+  A.links[1] = static_cast<const __half2 *>(N.links[1]);
+  A.in = static_cast<const bf16 *>(in);
+  A.out = static_cast<bf16 *>(out);
+  A.phi = static_cast<const bf16 *>(phi);
+  A.a = a;
+  A.partial = partial;
+  A.sample_stride = N.sample_stride;
+  A.batch = N.batch;
+  A.nsg = int((2u * unsigned(ctx->g.vh) + 15) / 16);
+  A.spw = stencil_spw(ctx, N.batch);
+  A.nitem = (A.nsg + 7) / 8 * ((N.batch + A.spw - 1) / A.spw);
+  const int blocks = 8 * std::min(128, (A.nitem + 3) / 4);  // at most 1024 (the partials' capacity)
+  if (phi) k_nn_stencil_mfma<true, true><<<blocks, kThreads, 0, ctx->stream>>>(A);
+  else if (adj) k_nn_stencil_mfma<true, false><<<blocks, kThreads, 0, ctx->stream>>>(A);
+  else k_nn_stencil_mfma<false, false><<<blocks, kThreads, 0, ctx->stream>>>(A);
+  LAUNCHCHK(ctx, "k_nn_stencil_mfma");
+  return blocks;
+}
+
 template <typename AT>
 int launch_stencil(hisq_ctx *ctx, const NNArgs &A, int prec, const void *in, void *out,
                    const float2 *a, bool adj) {
+  if (std::is_same<AT, bf16>::value && stencil_mfma(ctx, prec, A.batch, false)) {
+    const int rc = launch_stencil_mfma(ctx, A, in, out, a, adj, nullptr, nullptr);
+    return rc < 0 ? rc : HISQ_OK;
+  }
   const unsigned V = 2u * ctx->g.vh;
   dim3 grid((V + kThreads - 1) / kThreads * A.batch);
   const AT *i = static_cast<const AT *>(in);
@@ -1104,19 +1364,26 @@ int backward_t(hisq_ctx *ctx, int batch, const float2 *x32, const float2 *gz, un
   k_nn_embed<AT, true><<<gv, kThreads, 0, ctx->stream>>>(gz, gvs, static_cast<AT *>(gpsi), A, s->theta + s->off_out);
   LAUNCHCHK(ctx, "k_nn_embed");
   for (int l = s->layers - 1; l >= 0; --l) {
-    // stencil weights
-    if (prec == HISQ_F32)
-      k_nn_stencil_wgrad<AT, float2><<<nblk, kThreads, 0, ctx->stream>>>(
-          A, static_cast<const AT *>(b.phi[l]), static_cast<const AT *>(gpsi), partial);
-    else
-      k_nn_stencil_wgrad<AT, __half2><<<nblk, kThreads, 0, ctx->stream>>>(
-          A, static_cast<const AT *>(b.phi[l]), static_cast<const AT *>(gpsi), partial);
-    LAUNCHCHK(ctx, "k_nn_stencil_wgrad");
-    k_nn_sum_partials<<<9 * 2 * NC, kThreads, 0, ctx->stream>>>(partial, nblk, 9 * 2 * NC,
-                                                               s->grad + 2 * s->off_a[l], 1);
-    LAUNCHCHK(ctx, "k_nn_sum_partials");
-    // g_phi = S^dag g_psi
-    RETCHK(launch_stencil<AT>(ctx, A, prec, gpsi, gphi, s->theta + s->off_a[l], true));
+    // stencil weights and g_phi = S^dag g_psi
+    if (std::is_same<AT, bf16>::value && stencil_mfma(ctx, prec, batch, true)) {  // from the same link products
+      const int nb = launch_stencil_mfma(ctx, A, gpsi, gphi, s->theta + s->off_a[l], true, b.phi[l], partial);
+      if (nb < 0) return nb;
+      k_nn_sum_partials<<<9 * 2 * NC, kThreads, 0, ctx->stream>>>(partial, nb, 9 * 2 * NC,
+                                                                 s->grad + 2 * s->off_a[l], 1);
+      LAUNCHCHK(ctx, "k_nn_sum_partials");
+    } else {
+      if (prec == HISQ_F32)
+        k_nn_stencil_wgrad<AT, float2><<<nblk, kThreads, 0, ctx->stream>>>(
+            A, static_cast<const AT *>(b.phi[l]), static_cast<const AT *>(gpsi), partial);
+      else
+        k_nn_stencil_wgrad<AT, __half2><<<nblk, kThreads, 0, ctx->stream>>>(
+            A, static_cast<const AT *>(b.phi[l]), static_cast<const AT *>(gpsi), partial);
+      LAUNCHCHK(ctx, "k_nn_stencil_wgrad");
+      k_nn_sum_partials<<<9 * 2 * NC, kThreads, 0, ctx->stream>>>(partial, nblk, 9 * 2 * NC,
+                                                                 s->grad + 2 * s->off_a[l], 1);
+      LAUNCHCHK(ctx, "k_nn_sum_partials");
+      RETCHK(launch_stencil<AT>(ctx, A, prec, gpsi, gphi, s->theta + s->off_a[l], true));
+    }
     if (l >= 1) {
       // W_l: Q = sum g_phi_real psi_{l-1}_real^T, assembled into the complex gradient
       k_nn_mix_wgrad<AT><<<nblk, kThreads, 0, ctx->stream>>>(static_cast<const AT *>(gphi),

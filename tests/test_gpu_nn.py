@@ -5,6 +5,8 @@ training and save/load on the GPU.
 Tolerances: FP32 activation storage relative L2 1e-5 (forward) and 1e-4 (gradient vector);
 BF16 storage (MFMA channel mixing) relative L2 5e-2 and cosine similarity >= 0.999.
 """
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -277,3 +279,40 @@ def test_training_steps_match_oracle_adam():
     assert np.max(np.abs(d[keep])) <= tol
     assert np.max(np.abs(d)) <= 2.5 * lr
     lat.close()
+
+
+# ---- matrix-core training stencil (BF16 activations, FP16 links) --------------------------------------
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dims,n", [((4, 4, 4, 4), 1), ((4, 4, 4, 4), 5), ((6, 4, 4, 6), 3), ((4, 6, 10, 4), 4),
+                                    ((8, 8, 8, 10), 17)])
+@pytest.mark.parametrize("form", [hisq.HISQ_NN_FORM_DIRECT, hisq.HISQ_NN_FORM_GRAM])
+def test_matrix_core_stencil_against_the_general_kernels(dims, n, form):
+    """Loss and gradient with the FP16 link copy (matrix-core stencil, fused weight gradient) against
+    the same context with FP32 links holding the same values (the general kernels): sites that do
+    not fill the 16-site groups, batches of 1 to 17.  The links are rounded to FP16 first, so both
+    read the same numbers; products and sums are FP32 or better on both sides, so activations differ
+    by FP32 rounding and, through it, by rare BF16 rounding flips (2^-9 of a few of >= 10^4 values):
+    the gradients agree to 1e-3 of their norm, a dropped or misplaced hop shows at 10^-1."""
+    fat, naik = synth.gauge_links(dims, 91)
+    half = lambda u: (u.real.astype(np.float16).astype(np.float64)
+                      + 1j * u.imag.astype(np.float16).astype(np.float64))
+    lib = hisq.library()
+    rng = np.random.default_rng(4)
+    vh = int(np.prod(dims)) // 2
+    r = torch.from_numpy(rng.standard_normal((n, 3, vh)) + 1j * rng.standard_normal((n, 3, vh))).to(DEV)
+    y = torch.from_numpy(rng.standard_normal((n, 3, vh)) + 1j * rng.standard_normal((n, 3, vh))).to(DEV)
+    got = []
+    for copies in (hisq.HISQ_LINKS_F16, hisq.HISQ_LINKS_F32):
+        lat = hisq.Lattice(dims, 0)
+        lat.load_links(half(fat), half(naik), copies)
+        assert lib.hisq_nn_init(lat.ctx, 3, 8, 7) == 0
+        assert lib.hisq_nn_set_form(lat.ctx, form) == 0
+        nreal = 2 * lib.hisq_nn_num_params(lat.ctx)
+        loss, grad = ctypes.c_double(), (ctypes.c_double * nreal)()
+        assert lib.hisq_nn_loss_grad(lat.ctx, n, hisq._ptr(r), hisq._ptr(y), ctypes.byref(loss), grad) == 0
+        got.append((loss.value, np.array(grad[:])))
+        lat.close()
+    (l0, g0), (l1, g1) = got
+    assert abs(l0 - l1) <= 1e-3 * abs(l1)
+    assert np.linalg.norm(g0 - g1) <= 1e-3 * np.linalg.norm(g1)
