@@ -1306,16 +1306,28 @@ int launch_mix(hisq_ctx *ctx, const NNState *s, const void *in, void *out, size_
 }
 
 // Buffers: forward keeps phi_l and psi_l for every layer (2L activations) plus two gradient
-// buffers for the backward pass.
+// buffers for the backward pass.  With `second` (training) another set of phi and psi, so that two
+// forward passes can be kept at once; where the device cannot hold it, second is left without buffers.
 struct ActBufs {
   std::vector<void *> phi, psi;
   void *g0 = nullptr, *g1 = nullptr;
 };
 
-int act_bufs(hisq_ctx *ctx, int batch, bool train, ActBufs *b) {
+int act_bufs(hisq_ctx *ctx, int batch, bool train, ActBufs *b, ActBufs *second = nullptr) {
   NNState *s = ctx->nn;
   const size_t one = size_t(batch) * 3 * 2 * ctx->g.vh * NR * act_elem(s);
   const int count = train ? 2 * s->layers + 2 : 2;
+  if (second) {
+    const int rc = grow(ctx, &s->act, &s->act_bytes, one * (count + 2 * s->layers));
+    if (rc != HISQ_OK && rc != HISQ_ERR_OOM) return rc;
+    if (rc == HISQ_OK) {
+      char *base2 = static_cast<char *>(s->act) + one * count;
+      for (int l = 0; l < s->layers; ++l) {
+        second->phi.push_back(base2 + one * (2 * l));
+        second->psi.push_back(base2 + one * (2 * l + 1));
+      }
+    }
+  }
   RETCHK(grow(ctx, &s->act, &s->act_bytes, one * count));
   char *base = static_cast<char *>(s->act);
   b->phi.resize(s->layers);
@@ -1528,8 +1540,15 @@ int nn_batch_grad(hisq_ctx *ctx, int batch, const void *r, const void *y, bool f
   NNState *s = ctx->nn;
   Scratch sc;
   RETCHK(scratch(ctx, batch, &sc));
-  ActBufs b;
-  RETCHK(act_bufs(ctx, batch, true, &b));
+  // Gram form: the activations of N r (set br) are kept from the first pass to the last backward one
+  // beside those of N G, or computed again where they do not fit
+  ActBufs b, br;
+  RETCHK(act_bufs(ctx, batch, true, &b, s->form == HISQ_NN_FORM_GRAM ? &br : nullptr));
+  const bool kept = !br.phi.empty();
+  if (kept) {
+    br.g0 = b.g0;
+    br.g1 = b.g1;
+  }
   const size_t len = size_t(batch) * 3 * ctx->g.vh;
   const unsigned V = 2u * ctx->g.vh;
   const float2 *r32 = static_cast<const float2 *>(r), *y32 = static_cast<const float2 *>(y);
@@ -1552,7 +1571,7 @@ int nn_batch_grad(hisq_ctx *ctx, int batch, const void *r, const void *y, bool f
     LAUNCHCHK(ctx, "k_nn_sum_rows");
   }
   if (gram) {
-    RETCHK(forward(ctx, batch, r32, sc.u, true, b));
+    RETCHK(forward(ctx, batch, r32, sc.u, true, kept ? br : b));
     RETCHK(adjoint(ctx, batch, sc.u, sc.z32, b.g0, b.g1));
   } else {
     RETCHK(forward(ctx, batch, r32, sc.z32, false, b));
@@ -1578,8 +1597,8 @@ int nn_batch_grad(hisq_ctx *ctx, int batch, const void *r, const void *y, bool f
   if (gram) {
     RETCHK(forward(ctx, batch, sc.gz, sc.ng, true, b));
     RETCHK(backward(ctx, batch, sc.gz, sc.u, V, b, sc.partial, sc.partial_cap, sc.red));
-    RETCHK(forward(ctx, batch, r32, sc.u, true, b));  // caches for input r (u is no longer needed)
-    RETCHK(backward(ctx, batch, r32, sc.ng, V, b, sc.partial, sc.partial_cap, sc.red));
+    if (!kept) RETCHK(forward(ctx, batch, r32, sc.u, true, b));  // the activations again (u is not needed any more)
+    RETCHK(backward(ctx, batch, r32, sc.ng, V, kept ? br : b, sc.partial, sc.partial_cap, sc.red));
   } else {
     RETCHK(backward(ctx, batch, r32, sc.gz, unsigned(ctx->g.vh), b, sc.partial, sc.partial_cap, sc.red));
   }
