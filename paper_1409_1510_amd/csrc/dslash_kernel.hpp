@@ -905,8 +905,15 @@ template <int N, int I = 0, typename F> __device__ __forceinline__ void static_f
 typedef float f4a8_t __attribute__((ext_vector_type(4), aligned(8)));
 typedef unsigned u4_t __attribute__((ext_vector_type(4)));
 
-// Link entries of the two sites of a lane (LDS plane-major, sites adjacent).
+// Link entries of the sites of a lane (LDS plane-major, sites adjacent).
 template <typename LT> struct LinkPair;
+template <> struct LinkPair<double2> {
+  __device__ static void load(const double2 *p, double (&re)[1], double (&im)[1]) {
+    const double2 v = *p;
+    re[0] = v.x;
+    im[0] = v.y;
+  }
+};
 template <> struct LinkPair<float2> {
   __device__ static void load(const float2 *p, float (&re)[2], float (&im)[2]) {
     const float4 v = *reinterpret_cast<const float4 *>(p);
@@ -929,13 +936,30 @@ template <> struct LinkPair<__half2> {
 };
 
 // LDS of the pair form: as the whole-site form, with the neighbour table per pair of sites.
-constexpr size_t kNbrTablePairBytes = size_t(4) * 32 * sizeof(uint4);
+template <typename Real> constexpr size_t nbr_table_pair_bytes() {
+  return size_t(4) * (sizeof(Real) == 4 ? 32 : 64) * sizeof(uint4);
+}
 
 // Waves per SIMD of the pair form: 128 registers and 16 waves per CU (two workgroups of 8 waves with
-// FP32 links, four of 4 with FP16 links), or 256 registers and 8 waves with two rhs per lane, whose
-// gathers do not fit in 128.
+// FP32 links, four of 4 with FP16 links), or 256 registers and 8 waves with two FP32 rhs per lane, whose
+// gathers do not fit in 128.  FP64 links take a CU's LDS alone: one workgroup.
 template <typename LT, int RT> constexpr int pair_waves_per_simd(int wpb) {
-  return RT == 2 ? (wpb > 8 ? wpb / 4 : 2) : (wpb == 4 && sizeof(LT) > 4 ? 2 : 4);
+  return sizeof(LT) > 8 ? wpb / 4 : (RT == 2 ? (wpb > 8 ? wpb / 4 : 2) : (wpb == 4 && sizeof(LT) > 4 ? 2 : 4));
+}
+// Hops gathered ahead: as many as fit in the registers
+constexpr int kLook64 = 6;  // (3, 6 and 12: within 1 % of each other)
+template <typename LT, int RT, bool EPI> constexpr int pair_look(int wpb) {
+  if (sizeof(LT) > 8) return wpb == 16 ? (RT == 1 ? 2 : 1) : (RT == 1 ? kLook64 : 2);
+  return EPI ? 2 : 3;
+}
+// the (re, im) of site s of a lane's 16 gathered bytes
+__device__ inline void site_value(const v4u_t &x, int s, float &re, float &im) {
+  re = __uint_as_float(x[2 * s]);
+  im = __uint_as_float(x[2 * s + 1]);
+}
+__device__ inline void site_value(const v4u_t &x, int, double &re, double &im) {
+  re = __hiloint2double(int(x[1]), int(x[0]));
+  im = __hiloint2double(int(x[3]), int(x[2]));
 }
 
 // Whole-site LDS form with two neighbouring sites (2 i, 2 i + 1) per lane, for complex64 vectors
@@ -951,11 +975,18 @@ template <typename LT, int RT> constexpr int pair_waves_per_simd(int wpb) {
 //   * the two 32-lane halves of a wave take different rhs: lane (pair i, half h) computes rhs
 //     r0 + h RT + r of a tile of 2 RT; the rhs offset is in the buffer loads' vector offset, so a
 //     rhs past n reads past the buffer's range (returns 0) and is not stored.
+// FP64 runs the same kernel with one site per lane and one rhs group (its gathers are 16 bytes already;
+// 32^3 x 8, 8 rhs: 96.4 -> 94.5 us, fused M form 103.7 -> 98.6; 16 rhs: 135 -> 132 and 146 -> 138 us:
+// one workgroup fills a CU's LDS, so the link staging is not hidden).
 // Same hop order and FMA sequence per site and rhs as k_dslash, and the same tree over the 64
 // sites of a block for the fused <p, Mp> partials (bit-identical outputs).
-template <typename LT, int RT, int NR, bool EPI, int WPB, bool NT>
+template <typename Real, typename LT, int RT, int NR, bool EPI, int WPB, bool NT>
 __global__ void __launch_bounds__(64 * WPB, (pair_waves_per_simd<LT, RT>(WPB))) k_dslash_pair(Args a) {
-  using C = float2;
+  using C = typename CT<Real>::T;
+  using V16 = std::conditional_t<sizeof(Real) == 4, f4a8_t, d2v>;  // 16 bytes of a vector in memory
+  constexpr int S = 16 / int(sizeof(C));     // sites per lane, and rhs groups of a wave
+  constexpr int LPH = 64 / S;                // lanes of a group
+  constexpr unsigned CB = sizeof(C);
   constexpr int PL = lds_staged_planes(NR);
   constexpr int SPL = 16 / int(sizeof(LT));  // sites per lane, and planes per wave, of a staging load
   extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -965,18 +996,21 @@ __global__ void __launch_bounds__(64 * WPB, (pair_waves_per_simd<LT, RT>(WPB))) 
   if (!lds_block(a, sblk)) return;  // uniform for the whole workgroup
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int pi = lane & 31, h = lane >> 5;
+  const int pi = lane % LPH, h = S == 1 ? 0 : lane / LPH;
   const unsigned vh = g.vh;
   const unsigned s0 = unsigned(sblk) * 64;
   const LT *__restrict__ links = static_cast<const LT *>(a.links);
   const unsigned plane_bytes = vh * unsigned(sizeof(C));
-  // neighbour table of the 32 pairs, byte offsets within a colour plane: [0] the pair before, the
-  // pair itself, the pair after in its x row, and the row's parity; [mu] the pairs at +1, -1, +3, -3
-  uint4 *nbt = reinterpret_cast<uint4 *>(smem_raw + lds_nbr_offset<float, LT, NR>());
+  // neighbour table of the lanes' sites, byte offsets within a colour plane: [mu] the sites (pairs) at
+  // +1, -1, +3, -3; with pairs [0] is the pair before, the pair itself, the pair after in its x row,
+  // and the row's parity
+  uint4 *nbt = reinterpret_cast<uint4 *>(smem_raw + lds_nbr_offset<Real, LT, NR>());
   // ---- gathers of one tile: LOOK hops ahead of the arithmetic (the compiler alone keeps one hop in
-  // flight).  Hop i = 4 (mu - 1) + k of the y, z and t directions is held in slot i % (LOOK + 1).
-  constexpr int LOOK = EPI ? 2 : 3;
-  v4u_t v[LOOK + 1][RT][3], xm[RT][3], xc[RT][3], xp[RT][3];
+  // flight).  Hop i = 4 (mu - MU0) + k is held in slot i % (LOOK + 1).
+  constexpr int LOOK = pair_look<LT, RT, EPI>(WPB);
+  constexpr int NH = S == 2 ? 12 : 16;  // hops gathered one by one (with two sites per lane all but x)
+  constexpr int MU0 = S == 2 ? 1 : 0;
+  v4u_t v[LOOK + 1][RT][3], xm[S == 2 ? RT : 1][3], xc[S == 2 ? RT : 1][3], xp[S == 2 ? RT : 1][3];
   uint4 nb;
   bool odd;
   int pj = pi;
@@ -988,38 +1022,40 @@ __global__ void __launch_bounds__(64 * WPB, (pair_waves_per_simd<LT, RT>(WPB))) 
   };
   auto issue = [&](auto ic) {
     constexpr int i = decltype(ic)::value;
-    if constexpr (i % 4 == 0) nb = nbt[(1 + i / 4) * 32 + pj];
+    if constexpr (i % 4 == 0) nb = nbt[(MU0 + i / 4) * LPH + pj];
     const unsigned off = (i & 3) == 0 ? nb.x : ((i & 3) == 1 ? nb.y : ((i & 3) == 2 ? nb.z : nb.w));
 #pragma unroll
     for (int r = 0; r < RT; ++r)
 #pragma unroll
       for (int b = 0; b < 3; ++b) v[i % (LOOK + 1)][r][b] = gather(off, r, b);
   };
-  // the x pairs and the first LOOK hops of a tile; its buffer covers the rhs that exist (past the
+  // the x pairs (S = 2) and the first LOOK hops of a tile; its buffer covers the rhs that exist (past the
   // last tile none: the loads read nothing and return 0)
   auto start_tile = [&](int tile) {
-    const int r0 = min(tile * 2 * RT, a.n);
+    const int r0 = min(tile * S * RT, a.n);
     const char *in = static_cast<const char *>(a.in) + size_t(r0) * 3 * plane_bytes;
     rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(in), short(0),
-                                           int(unsigned(min(2 * RT, a.n - r0)) * 3u * plane_bytes), kBufWord3);
-    const uint4 nx = nbt[pj];
-    odd = nx.w != 0;
+                                           int(unsigned(min(S * RT, a.n - r0)) * 3u * plane_bytes), kBufWord3);
+    if constexpr (S == 2) {
+      const uint4 nx = nbt[pj];
+      odd = nx.w != 0;
 #pragma unroll
-    for (int r = 0; r < RT; ++r)
+      for (int r = 0; r < RT; ++r)
 #pragma unroll
-      for (int b = 0; b < 3; ++b) {
-        xm[r][b] = gather(nx.x, r, b);
-        xc[r][b] = gather(nx.y, r, b);
-        xp[r][b] = gather(nx.z, r, b);
-      }
+        for (int b = 0; b < 3; ++b) {
+          xm[r][b] = gather(nx.x, r, b);
+          xc[r][b] = gather(nx.y, r, b);
+          xp[r][b] = gather(nx.z, r, b);
+        }
+    }
     static_for<LOOK>([&](auto ic) { issue(ic); });
   };
   // the active rhs of a tile, one bit each (uniform: scalar loads)
   auto tile_mask = [&](int tile) -> unsigned {
     unsigned m = 0;
 #pragma unroll
-    for (int k = 0; k < 2 * RT; ++k) {
-      const int q = tile * 2 * RT + k;
+    for (int k = 0; k < S * RT; ++k) {
+      const int q = tile * S * RT + k;
       if (q < a.n && (!a.active || a.active[q])) m |= 1u << k;
     }
     return m;
@@ -1032,8 +1068,8 @@ __global__ void __launch_bounds__(64 * WPB, (pair_waves_per_simd<LT, RT>(WPB))) 
       mask = tile_mask(tile);
       if (mask) break;
       if constexpr (EPI) {
-        if (a.partial && lane < 2 * RT && tile * 2 * RT + lane < a.n)
-          a.partial[size_t(tile * 2 * RT + lane) * ((vh + 63) / 64) + sblk] = 0.0;
+        if (a.partial && lane < S * RT && tile * S * RT + lane < a.n)
+          a.partial[size_t(tile * S * RT + lane) * ((vh + 63) / 64) + sblk] = 0.0;
       }
     }
     return tile;
@@ -1070,9 +1106,9 @@ __global__ void __launch_bounds__(64 * WPB, (pair_waves_per_simd<LT, RT>(WPB))) 
       }
     };
     fetch(0);
-    if (wave < 4) {  // wave mu: two offsets per half
+    if (wave < 4) {  // wave mu: with two rhs groups each half writes two of the four offsets
       const int mu = wave;
-      const unsigned sp = s0 + 2 * pi < vh ? s0 + 2 * pi : 0u;  // first site of the pair (0 past the end)
+      const unsigned sp = s0 + S * pi < vh ? s0 + S * pi : 0u;  // first site of the lane (0 past the end)
       const unsigned q1 = fast_div(sp, a.div_xh);
       const unsigned q2 = fast_div(q1, a.div_y);
       const unsigned q3 = fast_div(q2, a.div_z);
@@ -1081,17 +1117,28 @@ __global__ void __launch_bounds__(64 * WPB, (pair_waves_per_simd<LT, RT>(WPB))) 
       const int z = int(q2 - q3 * unsigned(g.lz));
       const int t = int(q3);
       const unsigned rowbase = sp - unsigned(xh);
-      uint2 n;
-      if (mu == 0) {
-        n.x = h ? (rowbase + unsigned(xh + 2 >= g.lxh ? 0 : xh + 2)) * 8u
-                : (rowbase + unsigned(xh == 0 ? g.lxh - 2 : xh - 2)) * 8u;
-        n.y = h ? unsigned((y + z + t + a.out_parity) & 1) : sp * 8u;
+      const int par = (y + z + t + a.out_parity) & 1;
+      if constexpr (S == 2) {
+        uint2 n;
+        if (mu == 0) {
+          n.x = h ? (rowbase + unsigned(xh + 2 >= g.lxh ? 0 : xh + 2)) * CB
+                  : (rowbase + unsigned(xh == 0 ? g.lxh - 2 : xh - 2)) * CB;
+          n.y = h ? unsigned(par) : sp * CB;
+        } else {
+          const int d = h ? 3 : 1;
+          n.x = hop_site(g, mu, d, sp, rowbase, 0, y, z, t) * CB;
+          n.y = hop_site(g, mu, -d, sp, rowbase, 0, y, z, t) * CB;
+        }
+        reinterpret_cast<uint2 *>(nbt)[(mu * LPH + pi) * 2 + h] = n;
       } else {
-        const int d = h ? 3 : 1;
-        n.x = hop_site(g, mu, d, sp, rowbase, 0, y, z, t) * 8u;
-        n.y = hop_site(g, mu, -d, sp, rowbase, 0, y, z, t) * 8u;
+        const int x = 2 * xh + par;
+        uint4 n;
+        n.x = hop_site(g, mu, 1, sp, rowbase, x, y, z, t) * CB;
+        n.y = hop_site(g, mu, -1, sp, rowbase, x, y, z, t) * CB;
+        n.z = hop_site(g, mu, 3, sp, rowbase, x, y, z, t) * CB;
+        n.w = hop_site(g, mu, -3, sp, rowbase, x, y, z, t) * CB;
+        nbt[mu * LPH + pi] = n;
       }
-      reinterpret_cast<uint2 *>(nbt)[(mu * 32 + pi) * 2 + h] = n;
     }
     __syncthreads();
     tile = next_tile(wave);
@@ -1111,59 +1158,59 @@ __global__ void __launch_bounds__(64 * WPB, (pair_waves_per_simd<LT, RT>(WPB))) 
     for (int item = threadIdx.x; item < 8 * 64; item += 64 * WPB) {
       const int k = item >> 6, ln = item & 63;
       const unsigned site = s0 + ln;
-      Lnk<float> Lk;
-      load_naik<float, LT, NR, NT>(links, 8 + k, vh, site < vh ? site : 0u, Lk);
+      Lnk<Real> Lk;
+      load_naik<Real, LT, NR, NT>(links, 8 + k, vh, site < vh ? site : 0u, Lk);
 #pragma unroll
-      for (int e = 0; e < 9; ++e) row2[(k * 9 + e) * 64 + ln] = make_float2(Lk.re[e / 3][e % 3], Lk.im[e / 3][e % 3]);
+      for (int e = 0; e < 9; ++e) row2[(k * 9 + e) * 64 + ln] = C{Lk.re[e / 3][e % 3], Lk.im[e / 3][e % 3]};
     }
   }
   __syncthreads();
   if constexpr (NR == 14 || NR == 13) {
     for (int item = threadIdx.x; item < 8 * 64; item += 64 * WPB) {
       const int k = item >> 6, ln = item & 63;
-      Lnk<float> Lk;
-      load_naik<float, LT, NR, false>(sl, 8 + k, 64u, unsigned(ln), Lk);
+      Lnk<Real> Lk;
+      load_naik<Real, LT, NR, false>(sl, 8 + k, 64u, unsigned(ln), Lk);
 #pragma unroll
-      for (int b = 0; b < 3; ++b) row2[(k * 3 + b) * 64 + ln] = make_float2(Lk.re[2][b], Lk.im[2][b]);
+      for (int b = 0; b < 3; ++b) row2[(k * 3 + b) * 64 + ln] = C{Lk.re[2][b], Lk.im[2][b]};
     }
     __syncthreads();
   }
 
-  // entry (ra, b) of the link of hop k (0..15) for the two sites
-  auto link_entry = [&](int k, int ra, int b, float (&re)[2], float (&im)[2]) {
+  // entry (ra, b) of the link of hop k (0..15) for the lane's sites
+  auto link_entry = [&](int k, int ra, int b, Real (&re)[S], Real (&im)[S]) {
     if constexpr (NR == 9) {
       if (k >= 8) {
-        LinkPair<float2>::load(row2 + 2 * pj + ((k - 8) * 9 + ra * 3 + b) * 64, re, im);
+        LinkPair<C>::load(row2 + S * pj + ((k - 8) * 9 + ra * 3 + b) * 64, re, im);
         return;
       }
     } else if constexpr (NR != 18) {
       if (k >= 8 && ra == 2) {
-        LinkPair<float2>::load(row2 + 2 * pj + ((k - 8) * 3 + b) * 64, re, im);
+        LinkPair<C>::load(row2 + S * pj + ((k - 8) * 3 + b) * 64, re, im);
         return;
       }
     }
-    LinkPair<LT>::load(sl + 2 * pj + (link_plane(k, NR) + ra * 3 + b) * 64, re, im);
+    LinkPair<LT>::load(sl + S * pj + (link_plane(k, NR) + ra * 3 + b) * 64, re, im);
   };
   while (tile < a.ntiles) {
-    const int q0 = tile * 2 * RT + h * RT;  // this lane's first rhs
-    float acc_re[RT][2][3], acc_im[RT][2][3];
+    const int q0 = tile * S * RT + h * RT;  // this lane's first rhs
+    Real acc_re[RT][S][3], acc_im[RT][S][3];
 #pragma unroll
     for (int r = 0; r < RT; ++r)
 #pragma unroll
-      for (int s = 0; s < 2; ++s)
+      for (int s = 0; s < S; ++s)
 #pragma unroll
-        for (int c = 0; c < 3; ++c) acc_re[r][s][c] = acc_im[r][s][c] = 0.f;
+        for (int c = 0; c < 3; ++c) acc_re[r][s][c] = acc_im[r][s][c] = Real(0);
     // The arithmetic of a hop ends here for the scheduler, and the link reads of the next one start
     // (left to itself the compiler issues the LDS reads of all 16 hops at once and spills them).
     auto fence = [&] {
 #pragma unroll
       for (int r = 0; r < RT; ++r)
-        asm volatile("" : "+v"(acc_re[r][0][0]), "+v"(acc_re[r][0][1]), "+v"(acc_re[r][0][2]), "+v"(acc_im[r][0][0]),
-                     "+v"(acc_im[r][0][1]), "+v"(acc_im[r][0][2]), "+v"(acc_re[r][1][0]), "+v"(acc_re[r][1][1]),
-                     "+v"(acc_re[r][1][2]), "+v"(acc_im[r][1][0]), "+v"(acc_im[r][1][1]), "+v"(acc_im[r][1][2]),
-                     "+v"(pj));
+#pragma unroll
+        for (int s = 0; s < S; ++s)
+          asm volatile("" : "+v"(acc_re[r][s][0]), "+v"(acc_re[r][s][1]), "+v"(acc_re[r][s][2]), "+v"(acc_im[r][s][0]),
+                       "+v"(acc_im[r][s][1]), "+v"(acc_im[r][s][2]), "+v"(pj));
     };
-    // acc += sign * L x, x[r][b] = the pair's (re, im, re, im) (hops +1, -1, +3, -3 are k / 4 = 0 .. 3)
+    // acc += sign * L x, x[r][b] = the lane's sites (re, im) (hops +1, -1, +3, -3 are k / 4 = 0 .. 3)
     auto hop = [&](auto kc, const v4u_t (&x)[RT][3]) {
       constexpr int k = decltype(kc)::value;
       constexpr bool neg = (k / 4) & 1;
@@ -1171,19 +1218,20 @@ __global__ void __launch_bounds__(64 * WPB, (pair_waves_per_simd<LT, RT>(WPB))) 
       for (int ra = 0; ra < 3; ++ra) {
 #pragma unroll
         for (int b = 0; b < 3; ++b) {
-          float lre[2], lim[2];
+          Real lre[S], lim[S];
           link_entry(k, ra, b, lre, lim);
 #pragma unroll
-          for (int s = 0; s < 2; ++s) {
-            const float lr = neg ? -lre[s] : lre[s];
-            const float li = neg ? -lim[s] : lim[s];
+          for (int s = 0; s < S; ++s) {
+            const Real lr = neg ? -lre[s] : lre[s];
+            const Real li = neg ? -lim[s] : lim[s];
 #pragma unroll
             for (int r = 0; r < RT; ++r) {
-              const float vx = __uint_as_float(x[r][b][2 * s]), vy = __uint_as_float(x[r][b][2 * s + 1]);
-              acc_re[r][s][ra] = fmaf(lr, vx, acc_re[r][s][ra]);
-              acc_re[r][s][ra] = fmaf(-li, vy, acc_re[r][s][ra]);
-              acc_im[r][s][ra] = fmaf(lr, vy, acc_im[r][s][ra]);
-              acc_im[r][s][ra] = fmaf(li, vx, acc_im[r][s][ra]);
+              Real vx, vy;
+              site_value(x[r][b], s, vx, vy);
+              acc_re[r][s][ra] = fmaR(lr, vx, acc_re[r][s][ra]);
+              acc_re[r][s][ra] = fmaR(-li, vy, acc_re[r][s][ra]);
+              acc_im[r][s][ra] = fmaR(lr, vy, acc_im[r][s][ra]);
+              acc_im[r][s][ra] = fmaR(li, vx, acc_im[r][s][ra]);
             }
           }
         }
@@ -1191,41 +1239,43 @@ __global__ void __launch_bounds__(64 * WPB, (pair_waves_per_simd<LT, RT>(WPB))) 
       fence();
     };
     fence();
-    static_for<4>([&](auto kc) {  // x direction: +1, -1, +3, -3 from shifts of the row by -2..2 sites
-      constexpr int k = decltype(kc)::value;
-      v4u_t x[RT][3];
+    if constexpr (S == 2) {
+      static_for<4>([&](auto kc) {  // x direction: +1, -1, +3, -3 from shifts of the row by -2..2 sites
+        constexpr int k = decltype(kc)::value;
+        v4u_t x[RT][3];
 #pragma unroll
-      for (int r = 0; r < RT; ++r)
+        for (int r = 0; r < RT; ++r)
 #pragma unroll
-        for (int b = 0; b < 3; ++b) {
-          const v4u_t M = xm[r][b], Z = xc[r][b], P = xp[r][b];
-          const v4u_t lo = {M[2], M[3], Z[0], Z[1]}, hi = {Z[2], Z[3], P[0], P[1]};  // shifts -1, +1
-          const v4u_t u = k == 0 ? hi : (k == 1 ? Z : (k == 2 ? P : lo));  // rows of odd parity
-          const v4u_t w = k == 0 ? Z : (k == 1 ? lo : (k == 2 ? hi : M));  // rows of even parity
+          for (int b = 0; b < 3; ++b) {
+            const v4u_t M = xm[r][b], Z = xc[r][b], P = xp[r][b];
+            const v4u_t lo = {M[2], M[3], Z[0], Z[1]}, hi = {Z[2], Z[3], P[0], P[1]};  // shifts -1, +1
+            const v4u_t u = k == 0 ? hi : (k == 1 ? Z : (k == 2 ? P : lo));  // rows of odd parity
+            const v4u_t w = k == 0 ? Z : (k == 1 ? lo : (k == 2 ? hi : M));  // rows of even parity
 #pragma unroll
-          for (int e = 0; e < 4; ++e) x[r][b][e] = odd ? u[e] : w[e];
-        }
-      hop(std::integral_constant<int, 4 * k>{}, x);
-    });
-    const bool valid = s0 + 2 * pi < vh;
+            for (int e = 0; e < 4; ++e) x[r][b][e] = odd ? u[e] : w[e];
+          }
+        hop(std::integral_constant<int, 4 * k>{}, x);
+      });
+    }
+    const bool valid = s0 + S * pi < vh;
     bool act[RT];
 #pragma unroll
     for (int r = 0; r < RT; ++r) act[r] = valid && ((mask >> (h * RT + r)) & 1u);
-    const size_t tile_off = size_t(q0) * 3 * vh + s0 + 2 * pi;  // the lane's first output
-    f4a8_t pv[RT][3];
-    static_for<12>([&](auto ic) {
+    const size_t tile_off = size_t(q0) * 3 * vh + s0 + S * pi;  // the lane's first output
+    V16 pv[RT][3];
+    static_for<NH>([&](auto ic) {
       constexpr int i = decltype(ic)::value;
-      if constexpr (i + LOOK < 12) issue(std::integral_constant<int, i + LOOK>{});
-      if constexpr (EPI && i + LOOK == 12) {
+      if constexpr (i + LOOK < NH) issue(std::integral_constant<int, i + LOOK>{});
+      if constexpr (EPI && i + LOOK == NH) {
         const C *p = static_cast<const C *>(a.pvec) + tile_off;
 #pragma unroll
         for (int r = 0; r < RT; ++r)
           if (act[r]) {
 #pragma unroll
-            for (int c = 0; c < 3; ++c) pv[r][c] = *reinterpret_cast<const f4a8_t *>(p + size_t(r * 3 + c) * vh);
+            for (int c = 0; c < 3; ++c) pv[r][c] = *reinterpret_cast<const V16 *>(p + size_t(r * 3 + c) * vh);
           }
       }
-      hop(std::integral_constant<int, 4 * (i & 3) + 1 + i / 4>{}, v[i % (LOOK + 1)]);
+      hop(std::integral_constant<int, 4 * (i & 3) + MU0 + i / 4>{}, v[i % (LOOK + 1)]);
     });
     const int done = tile;
     tile = next_tile(tile + WPB);
@@ -1237,41 +1287,47 @@ __global__ void __launch_bounds__(64 * WPB, (pair_waves_per_simd<LT, RT>(WPB))) 
         if (!act[r]) continue;
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
-          const f4a8_t o = {acc_re[r][0][c], acc_im[r][0][c], acc_re[r][1][c], acc_im[r][1][c]};
-          *reinterpret_cast<f4a8_t *>(out + size_t(r * 3 + c) * vh) = o;
+          V16 o;
+#pragma unroll
+          for (int s = 0; s < S; ++s) {
+            o[2 * s] = acc_re[r][s][c];
+            o[2 * s + 1] = acc_im[r][s][c];
+          }
+          *reinterpret_cast<V16 *>(out + size_t(r * 3 + c) * vh) = o;
         }
       }
     } else {
-      const float m2 = float(a.mass2);
+      const Real m2 = Real(a.mass2);
       const unsigned nw = (vh + 63) / 64;
 #pragma unroll
       for (int r = 0; r < RT; ++r) {
-        double d0 = 0.0, d1 = 0.0;
+        double d[S];
+#pragma unroll
+        for (int s = 0; s < S; ++s) d[s] = 0.0;
         if (act[r]) {
 #pragma unroll
           for (int c = 0; c < 3; ++c) {
-            const f4a8_t p = pv[r][c];
-            f4a8_t o;
-            o.x = fmaf(m2, p.x, -acc_re[r][0][c]);
-            o.y = fmaf(m2, p.y, -acc_im[r][0][c]);
-            o.z = fmaf(m2, p.z, -acc_re[r][1][c]);
-            o.w = fmaf(m2, p.w, -acc_im[r][1][c]);
-            *reinterpret_cast<f4a8_t *>(out + size_t(r * 3 + c) * vh) = o;
-            d0 = fma(double(p.x), double(o.x), d0);
-            d0 = fma(double(p.y), double(o.y), d0);
-            d1 = fma(double(p.z), double(o.z), d1);
-            d1 = fma(double(p.w), double(o.w), d1);
+            const V16 p = pv[r][c];
+            V16 o;
+#pragma unroll
+            for (int s = 0; s < S; ++s) {
+              o[2 * s] = fmaR(m2, p[2 * s], -acc_re[r][s][c]);
+              o[2 * s + 1] = fmaR(m2, p[2 * s + 1], -acc_im[r][s][c]);
+              d[s] = fma(double(p[2 * s]), double(o[2 * s]), d[s]);
+              d[s] = fma(double(p[2 * s + 1]), double(o[2 * s + 1]), d[s]);
+            }
+            *reinterpret_cast<V16 *>(out + size_t(r * 3 + c) * vh) = o;
           }
         }
         if (a.partial) {
-          // the one-site form's tree: site s + site (s + 32), ..., s + (s + 2), then site 0 + site 1
+          // the tree of k_dslash over the 64 sites: site s + site (s + 32), then + (s + 16), ..., + (s + 1)
 #pragma unroll
-          for (int off = 16; off > 0; off >>= 1) {
-            d0 += __shfl_down(d0, off, 64);
-            d1 += __shfl_down(d1, off, 64);
+          for (int off = LPH / 2; off > 0; off >>= 1) {
+#pragma unroll
+            for (int s = 0; s < S; ++s) d[s] += __shfl_down(d[s], off, 64);
           }
-          if (pi == 0 && done * 2 * RT + h * RT + r < a.n)
-            a.partial[size_t(done * 2 * RT + h * RT + r) * nw + sblk] = d0 + d1;
+          if (pi == 0 && done * S * RT + h * RT + r < a.n)
+            a.partial[size_t(done * S * RT + h * RT + r) * nw + sblk] = S == 2 ? d[0] + d[S - 1] : d[0];
         }
       }
     }
@@ -1594,10 +1650,10 @@ void launch_t(const Args &a, dim3 grid, hipStream_t st) {
 
 template <typename Real, typename LT, int RT, int NR, bool EPI, int WPB, bool NT>
 void launch_lds(const Args &a, dim3 grid, hipStream_t st) {
-  if constexpr (sizeof(Real) == 4 && RT >= 2) {
-    if (a.g.lx % 4 == 0) {
-      k_dslash_pair<LT, RT / 2, NR, EPI, WPB, NT>
-          <<<grid, 64 * WPB, lds_nbr_offset<float, LT, NR>() + kNbrTablePairBytes, st>>>(a);
+  if constexpr (sizeof(Real) == 8 ? RT <= 2 : RT >= 2) {
+    if (sizeof(Real) == 8 || a.g.lx % 4 == 0) {
+      k_dslash_pair<Real, LT, sizeof(Real) == 8 ? RT : RT / 2, NR, EPI, WPB, NT>
+          <<<grid, 64 * WPB, lds_nbr_offset<Real, LT, NR>() + nbr_table_pair_bytes<Real>(), st>>>(a);
       return;
     }
   }
