@@ -31,8 +31,8 @@ FLAGS = [
 
 
 # per-unit scheduler: the FP64 Dslash instances are scheduled for instruction-level parallelism
-# (LLVM's max-ilp strategy), which issues their 16-byte gathers earlier: measured 11-19 % faster
-# FP64 LDS launches at 8 and 16 rhs (32^3 x 8) and within 1 % at 1-4 rhs.  The FP32 and FP16-link
+# (LLVM's max-ilp strategy), measured 1.7-2.4 % faster FP64 LDS launches at 8 and 16 rhs
+# (32^3 x 8: 94.5 us against 96.1, fused M 98.6 against 101.0, 16 rhs 132 against 135).  The FP32 and FP16-link
 # units keep the default strategy, under which their 16-rhs launches are 8-10 % faster than with
 # max-ilp.  Scheduling only orders instructions: every output stays bit-identical.
 EXTRA_FLAGS = {"dslash_f64.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"]}

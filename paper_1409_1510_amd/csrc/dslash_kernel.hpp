@@ -539,6 +539,118 @@ __global__ void __launch_bounds__(256) k_dslash(Args a) {
   }
 }
 
+// Row form of the register-tile kernel (one rhs per thread, 18-real links) for launches too small to
+// fill the chip: one rhs of 64 sites is a workgroup of three waves, wave w computing row w of every
+// hop.  What bounds such a launch is its serial chain, not a rate: k_dslash waits for memory hop by
+// hop, and the LDS forms stage all 144 link planes of 64 sites before the few waves that hold a rhs
+// tile start.  Here every load of the kernel (16 gathers and 48 link entries a lane) is in flight
+// at once, and a third of the link loads and FMAs is left on each wave.  The links, used by one wave
+// each, stay in registers; the gathered vectors, used by all three, are loaded once (component w by
+// wave w) and exchanged through LDS.  Each row keeps its FMA order, and the fused form sums <p, q> over
+// the rows in wave 0 in the order of k_dslash: same bits.
+// Half Dslash, microseconds, the fastest other form -> this (MI355X): 8^4, 1 rhs: FP64 5.6 -> 4.3, fused
+// M 6.7 -> 4.6, FP32 6.2 -> 4.2, FP16 links 5.4 -> 3.7; 8^4, 8 rhs: 6.6 -> 5.0, 6.8 -> 4.5, 6.8 -> 4.0;
+// 16^4, 1 rhs: 14.5 -> 13.4, 10.8 -> 8.0, 7.7 -> 5.9.
+template <typename Real, typename LT, bool EPI, bool NT>
+__global__ void __launch_bounds__(192) k_dslash_rows(Args a) {
+  using C = typename CT<Real>::T;
+  __shared__ C vs[48 * 64];
+  const Geometry &g = a.g;
+  const int chunk = gridDim.x >> 3;
+  const int lb = (blockIdx.x & 7) * chunk + (blockIdx.x >> 3);
+  if (lb >= a.nsblk * a.ntiles) return;  // uniform for the whole workgroup
+  const int sblk = lb / a.ntiles;
+  const int r = lb - sblk * a.ntiles;
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const unsigned vh = g.vh;
+  const bool valid = sblk * 64u + lane < vh;
+  const unsigned s = valid ? sblk * 64u + lane : vh - 1;
+  const unsigned nw = (vh + 63) / 64;
+  if (a.active && !a.active[r]) {  // uniform
+    if constexpr (EPI) {
+      if (a.partial && threadIdx.x == 0) a.partial[size_t(r) * nw + sblk] = 0.0;
+    }
+    return;
+  }
+  const size_t off = size_t(r) * 3 * vh + size_t(w) * vh;
+  const C *__restrict__ in = static_cast<const C *>(a.in) + off;
+  const LT *__restrict__ lk = static_cast<const LT *>(a.links) + size_t(w) * 3 * vh + s;
+
+  const unsigned row = fast_div(s, a.div_xh);
+  const int xh = int(s - row * g.lxh);
+  const unsigned rz = fast_div(row, a.div_y);
+  const int y = int(row - rz * g.ly);
+  const unsigned t = fast_div(rz, a.div_z);
+  const int z = int(rz - t * g.lz);
+  const int x = 2 * xh + ((y + z + int(t) + a.out_parity) & 1);
+  C v[16];
+#pragma unroll
+  for (int mu = 0; mu < 4; ++mu) {
+    unsigned f1, b1, f3, b3;
+    hop_sites(g, mu, s, s - xh, x, y, z, int(t), f1, b1, f3, b3);
+    v[mu * 4] = in[f1];
+    v[mu * 4 + 1] = in[b1];
+    v[mu * 4 + 2] = in[f3];
+    v[mu * 4 + 3] = in[b3];
+  }
+  Real lr[16][3], li[16][3];
+#pragma unroll
+  for (int h = 0; h < 16; ++h)
+#pragma unroll
+    for (int b = 0; b < 3; ++b)  // in the order of use: hop h % 4 of direction h / 4
+      ld_link<NT>(lk + size_t(link_plane((h & 3) * 4 + (h >> 2), 18) + b) * vh, lr[h][b], li[h][b]);
+  C p;
+  if constexpr (EPI) p = (static_cast<const C *>(a.pvec) + off)[s];
+#pragma unroll
+  for (int h = 0; h < 16; ++h) vs[(h * 3 + w) * 64 + lane] = v[h];
+  __syncthreads();
+
+  Real re = Real(0), im = Real(0);
+#pragma unroll
+  for (int h = 0; h < 16; ++h)
+#pragma unroll
+    for (int b = 0; b < 3; ++b) {
+      const C u = vs[(h * 3 + b) * 64 + lane];
+      const Real xr = (h & 1) ? -lr[h][b] : lr[h][b];
+      const Real xi = (h & 1) ? -li[h][b] : li[h][b];
+      re = fmaR(xr, u.x, re);
+      re = fmaR(-xi, u.y, re);
+      im = fmaR(xr, u.y, im);
+      im = fmaR(xi, u.x, im);
+    }
+  C o;
+  if constexpr (!EPI) {
+    o.x = re;
+    o.y = im;
+    if (valid) (static_cast<C *>(a.out) + off)[s] = o;
+  } else {
+    const Real m2 = Real(a.mass2);
+    o.x = fmaR(m2, p.x, -re);
+    o.y = fmaR(m2, p.y, -im);
+    if (valid) (static_cast<C *>(a.out) + off)[s] = o;
+    if (a.partial) {
+      __syncthreads();  // every wave has read its vectors
+      vs[w * 64 + lane] = o;
+      vs[(3 + w) * 64 + lane] = p;
+      __syncthreads();
+      if (w == 0) {
+        double d = 0.0;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          const C oc = vs[c * 64 + lane], pc = vs[(3 + c) * 64 + lane];
+          d = fma(double(pc.x), double(oc.x), d);
+          d = fma(double(pc.y), double(oc.y), d);
+        }
+        if (!valid) d = 0.0;
+#pragma unroll
+        for (int o2 = 32; o2 > 0; o2 >>= 1) d += __shfl_down(d, o2, 64);
+        if (lane == 0) a.partial[size_t(r) * nw + sblk] = d;
+      }
+    }
+  }
+}
+
 // Word 3 of a raw buffer descriptor on CDNA (32-bit data format, no swizzle, no stride): a
 // plain byte-addressed range checked against its size.
 constexpr int kBufWord3 = 0x00020000;
@@ -1641,24 +1753,40 @@ __global__ void __launch_bounds__(64 * WPB, (WPB == 16 && TPW == 1) ? 8 : 1) k_d
   }
 }
 
+// Row form up to this many workgroups (64-site blocks times rhs), the number that is resident at two
+// per CU in FP64, twice that for the smaller links.  FP64: 512 (16^4, 1 rhs) 13.4 us against 14.5 with
+// k_dslash, fused 14.2 against 15.2; 1024 (2 rhs) fused slower than its 16.6, and the LDS forms are
+// ahead from 648 (12^4, 4 rhs: 9.0 against 9.3).  FP32: 1024 (16^4, 2 rhs) 9.6 against 11.3 of the LDS
+// forms, FP16 links 7.6 against 9.1; 1296 (12^4, 8 rhs) 12.3 against 9.4, 9.0 against 8.6.
+template <typename Real> constexpr int kRowsMaxBlocks = sizeof(Real) == 8 ? 512 : 1024;
+
 using DslashFn = void (*)(const Args &, dim3, hipStream_t);
 
 template <typename Real, typename LT, int RT, int NR, bool EPI, int SPB, bool NT>
 void launch_t(const Args &a, dim3 grid, hipStream_t st) {
+  if constexpr (RT == 1 && NR == 18 && SPB == 64) {
+    if (a.nsblk * a.ntiles <= kRowsMaxBlocks<Real>) {
+      k_dslash_rows<Real, LT, EPI, NT><<<(a.nsblk * a.ntiles + 7) / 8 * 8, 192, 0, st>>>(a);
+      return;
+    }
+  }
   k_dslash<Real, LT, RT, NR, EPI, SPB, NT><<<grid, 256, 0, st>>>(a);
 }
 
 template <typename Real, typename LT, int RT, int NR, bool EPI, int WPB, bool NT>
 void launch_lds(const Args &a, dim3 grid, hipStream_t st) {
-  if constexpr (sizeof(Real) == 8 ? RT <= 2 : RT >= 2) {
-    if (sizeof(Real) == 8 || a.g.lx % 4 == 0) {
-      k_dslash_pair<Real, LT, sizeof(Real) == 8 ? RT : RT / 2, NR, EPI, WPB, NT>
+  constexpr bool f64 = sizeof(Real) == 8;
+  if constexpr (f64 ? RT <= 2 : RT >= 2) {
+    if (f64 || a.g.lx % 4 == 0) {
+      k_dslash_pair<Real, LT, f64 ? RT : RT / 2, NR, EPI, WPB, NT>
           <<<grid, 64 * WPB, lds_nbr_offset<Real, LT, NR>() + nbr_table_pair_bytes<Real>(), st>>>(a);
       return;
     }
   }
-  constexpr size_t lds = lds_nbr_offset<Real, LT, NR>() + kNbrTableBytes;
-  k_dslash_lds<Real, LT, RT, NR, EPI, WPB, NT><<<grid, 64 * WPB, lds, st>>>(a);
+  if constexpr (!f64 || RT > 2) {
+    constexpr size_t lds = lds_nbr_offset<Real, LT, NR>() + kNbrTableBytes;
+    k_dslash_lds<Real, LT, RT, NR, EPI, WPB, NT><<<grid, 64 * WPB, lds, st>>>(a);
+  }
 }
 
 template <typename Real, typename LT, int RT, bool R14, bool EPI, int WPB, int TPW, bool NT>

@@ -574,3 +574,52 @@ def test_pair_form_is_bit_identical(dims, recon):
                     assert torch.equal(torch.view_as_real(a) if a.is_complex() else a,
                                        torch.view_as_real(b) if b.is_complex() else b), (cfg, prec, n)
     lat.close()
+
+
+# ---- launches too small to fill the chip: three waves per 64 sites, one per row --------------------
+
+def _bits_over_configs(lat, prec, n, cfgs, g):
+    """Both halves, M v and <v, Mv> of every configuration equal to the first one's, bit for bit."""
+    v = torch.randn(n, 3, lat.vh, generator=g, device=DEV,
+                    dtype=torch.complex128 if prec == hisq.HISQ_F64 else torch.complex64)
+    ref = None
+    for cfg in cfgs:
+        hisq.hisq_set_launch(lat.ctx, prec, n, cfg)
+        out = torch.zeros_like(v)
+        got = []
+        for par in (1, 0):
+            lat.dslash(par, prec, v, out)
+            got.append(torch.view_as_real(out).clone())
+        q, pq = lat.apply_m(prec, 0.3, v, out, with_pq=True)
+        got += [torch.view_as_real(q).clone(), pq]
+        ref = ref or got
+        for a, b in zip(got, ref):
+            assert torch.equal(a, b), (cfg, prec, n)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dims,counts", [((4, 4, 4, 4), (1, 64)), ((6, 4, 10, 6), (1, 5, 43, 44)),
+                                         ((8, 8, 8, 8), (1, 16, 17, 32, 33)), ((30, 10, 6, 4), (1, 9, 18, 19))])
+def test_row_form_is_bit_identical(dims, counts):
+    """64-site blocks times rhs up to and past the row form's limits (512 in FP64, 1024), and a
+    partial last block; (1, 256, ...) is the register-tile kernel at every size."""
+    lat, _, _ = make_lattice(dims, 78, recon=18)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(6)
+    for prec in (hisq.HISQ_F64, hisq.HISQ_F32, hisq.HISQ_F16):
+        for n in counts:
+            _bits_over_configs(lat, prec, n, [(1, 256, 0, 0, 0), (1, 64, 0, 0, 0), (1, 64, 1, 0, 0)], g)
+    lat.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dims", [(4, 4, 4, 4), (6, 4, 10, 6), (30, 10, 6, 4)])
+def test_fp64_gather_ahead_form_is_bit_identical(dims):
+    """The FP64 LDS form (one site per lane, gathers ahead) with partial rhs tiles and blocks."""
+    lat, _, _ = make_lattice(dims, 79, recon=18)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(7)
+    for n in (1, 2, 3, 9, 17):
+        _bits_over_configs(lat, hisq.HISQ_F64, n, [(1, 256, 0, 0, 0)] + [
+            (rt, 64, nt, lds, 0) for rt in (1, 2) for nt in (0, 1) for lds in (1, 2, 3)], g)
+    lat.close()
