@@ -860,8 +860,8 @@ def main():
             result["roofline_64x64x64x16"] = {
                 "bound": "hbm", "achieved": e["compulsory_GBps"], "peak": 8000.0, "unit": "GB/s",
                 "frac": round(e["compulsory_GBps"] / 8000.0, 4),
-                "kernel": "k_dslash_lds (half Dslash, FP32, 16 rhs)", "launch": e["launch"],
-                "counters": "profiles/k_dslash_f32_n16_64x64x64x16.txt"}
+                "kernel": "k_dslash_pair (half Dslash, FP32, 16 rhs)", "launch": e["launch"],
+                "counters": "profiles/k_dslash_f32_n16_64x64x64x16.txt (k_dslash_lds)"}
 
     if not args.no_cg:
         c2 = synth.WORKLOADS["c2"]
