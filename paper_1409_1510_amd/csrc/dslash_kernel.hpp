@@ -1004,6 +1004,21 @@ __global__ void __launch_bounds__(64 * WPB, WPB / 4 * (sizeof(LT) > 8 ? 1 : 2)) 
   }
 }
 
+// Window of the buffer loads of the rhs tile `tile` (of `width` rhs, n in all): its first rhs, the bytes
+// of the rhs that exist, and the scalar offset from one colour plane to the next.  A wave without a
+// tile (tile * width >= n) gets an empty window and must have step 0: a raw buffer load compares its
+// vector offset with the window's size minus the scalar offset, and 0 bytes minus a plane wraps
+// round to a range that lets the load through, past the caller's vector.
+struct TileWindow {
+  int rhs;
+  unsigned bytes, step;
+};
+__host__ __device__ constexpr TileWindow tile_window(int tile, int width, int n, unsigned plane_bytes) {
+  const int r0 = tile * width < n ? tile * width : n;
+  const int live = n - r0 < width ? n - r0 : width;
+  return {r0, unsigned(live) * 3u * plane_bytes, live > 0 ? plane_bytes : 0u};
+}
+
 // f(integral_constant 0), ..., f(integral_constant N - 1)
 template <int N, int I = 0, typename F> __device__ __forceinline__ void static_for(F &&f) {
   if constexpr (I < N) {
@@ -1128,26 +1143,26 @@ __global__ void __launch_bounds__(64 * WPB, (pair_waves_per_simd<LT, RT>(WPB))) 
   int pj = pi;
   __amdgpu_buffer_rsrc_t rs;
   const unsigned hoff = unsigned(h * RT * 3) * plane_bytes;
-  auto gather = [&](unsigned off, int r, int b) -> v4u_t {
+  auto gather = [&](unsigned off, int r, int b, unsigned step) -> v4u_t {
     return __builtin_amdgcn_raw_buffer_load_b128(rs, off + hoff + unsigned(r * 3) * plane_bytes,
-                                                 unsigned(b) * plane_bytes, 0);
+                                                 unsigned(b) * step, 0);
   };
-  auto issue = [&](auto ic) {
+  auto issue = [&](auto ic, unsigned step) {
     constexpr int i = decltype(ic)::value;
     if constexpr (i % 4 == 0) nb = nbt[(MU0 + i / 4) * LPH + pj];
     const unsigned off = (i & 3) == 0 ? nb.x : ((i & 3) == 1 ? nb.y : ((i & 3) == 2 ? nb.z : nb.w));
 #pragma unroll
     for (int r = 0; r < RT; ++r)
 #pragma unroll
-      for (int b = 0; b < 3; ++b) v[i % (LOOK + 1)][r][b] = gather(off, r, b);
+      for (int b = 0; b < 3; ++b) v[i % (LOOK + 1)][r][b] = gather(off, r, b, step);
   };
   // the x pairs (S = 2) and the first LOOK hops of a tile; its buffer covers the rhs that exist (past the
-  // last tile none: the loads read nothing and return 0)
-  auto start_tile = [&](int tile) {
-    const int r0 = min(tile * S * RT, a.n);
-    const char *in = static_cast<const char *>(a.in) + size_t(r0) * 3 * plane_bytes;
-    rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(in), short(0),
-                                           int(unsigned(min(S * RT, a.n - r0)) * 3u * plane_bytes), kBufWord3);
+  // last tile none: the loads read nothing and return 0).  step: the window's, or plane_bytes where the
+  // tile is known to exist
+  auto start_tile = [&](int tile, unsigned step) {
+    const TileWindow w = tile_window(tile, S * RT, a.n, plane_bytes);
+    const char *in = static_cast<const char *>(a.in) + size_t(w.rhs) * 3 * plane_bytes;
+    rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(in), short(0), int(w.bytes), kBufWord3);
     if constexpr (S == 2) {
       const uint4 nx = nbt[pj];
       odd = nx.w != 0;
@@ -1155,12 +1170,12 @@ __global__ void __launch_bounds__(64 * WPB, (pair_waves_per_simd<LT, RT>(WPB))) 
       for (int r = 0; r < RT; ++r)
 #pragma unroll
         for (int b = 0; b < 3; ++b) {
-          xm[r][b] = gather(nx.x, r, b);
-          xc[r][b] = gather(nx.y, r, b);
-          xp[r][b] = gather(nx.z, r, b);
+          xm[r][b] = gather(nx.x, r, b, step);
+          xc[r][b] = gather(nx.y, r, b, step);
+          xp[r][b] = gather(nx.z, r, b, step);
         }
     }
-    static_for<LOOK>([&](auto ic) { issue(ic); });
+    static_for<LOOK>([&](auto ic) { issue(ic, step); });
   };
   // the active rhs of a tile, one bit each (uniform: scalar loads)
   auto tile_mask = [&](int tile) -> unsigned {
@@ -1261,7 +1276,8 @@ __global__ void __launch_bounds__(64 * WPB, (pair_waves_per_simd<LT, RT>(WPB))) 
         fetch(c0 + CH);
       }
     }
-    start_tile(tile);  // also without a tile: a branch here would make the waits below cover the gathers
+    // also without a tile: a branch here would make the waits below cover the gathers
+    start_tile(tile, tile_window(tile, S * RT, a.n, plane_bytes).step);
     stash((PW - 1) / CH * CH);
   }
   // compressed Naik links: rebuilt once per site, as in the one-site form
@@ -1377,7 +1393,7 @@ __global__ void __launch_bounds__(64 * WPB, (pair_waves_per_simd<LT, RT>(WPB))) 
     V16 pv[RT][3];
     static_for<NH>([&](auto ic) {
       constexpr int i = decltype(ic)::value;
-      if constexpr (i + LOOK < NH) issue(std::integral_constant<int, i + LOOK>{});
+      if constexpr (i + LOOK < NH) issue(std::integral_constant<int, i + LOOK>{}, plane_bytes);
       if constexpr (EPI && i + LOOK == NH) {
         const C *p = static_cast<const C *>(a.pvec) + tile_off;
 #pragma unroll
@@ -1391,7 +1407,7 @@ __global__ void __launch_bounds__(64 * WPB, (pair_waves_per_simd<LT, RT>(WPB))) 
     });
     const int done = tile;
     tile = next_tile(tile + WPB);
-    if (tile < a.ntiles) start_tile(tile);
+    if (tile < a.ntiles) start_tile(tile, plane_bytes);
     C *out = static_cast<C *>(a.out) + tile_off;
     if constexpr (!EPI) {
 #pragma unroll
