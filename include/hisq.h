@@ -82,6 +82,12 @@ const char *hisq_last_error(const hisq_ctx *ctx);
 /* Change the stream later calls enqueue on. */
 int hisq_set_stream(hisq_ctx *ctx, void *hip_stream);
 
+/* Device memory the context may hold at once, in bytes (0, the default: as much as the device gives).
+ * An allocation that would pass it fails with HISQ_ERR_OOM, as one that the device refuses does;
+ * memory a call can do without (see hisq_nn_loss_grad) is left out instead.  What the context
+ * already holds is kept. */
+int hisq_set_memory_limit(hisq_ctx *ctx, size_t bytes);
+
 /* Copy the fat links X and Naik links N (Section 1, Eq. 3) into the context.
  *   fat, naik : [V][4][3][3] complex128, host or device memory (detected), read only.
  *   copies    : HISQ_LINKS_* mask of device copies to build (FP64 is needed by HISQ_F64 calls
@@ -294,7 +300,11 @@ int hisq_nn_set_loss(hisq_ctx *ctx, int kind, double mass);
 int hisq_nn_apply(hisq_ctx *ctx, int n, int prec_io, const void *r, void *z);
 /* Loss (see hisq_nn_set_loss) and its gradient with respect to the parameters (Wirtinger:
  * dL/dRe + i dL/dIm, 2 * num_params reals, host) for n pairs r, y (device complex128
- * [n][3][V/2]).  loss and grad may be NULL.  Synchronises. */
+ * [n][3][V/2]).  loss and grad may be NULL.  Synchronises.
+ * Memory: 2 L + 2 activations of n * 3 * V * 8 complex numbers (BF16: 4 bytes each), and in the Gram form
+ * 2 L more while at least a quarter of the device stays free beside them (15 % less time at 32^3 x 8 with
+ * 16 pairs and L = 4; the result is the same, bit for bit).  The context gives these back when one of
+ * its other allocations needs the memory, when hisq_nn_train returns (above 64 MiB) and with the network. */
 int hisq_nn_loss_grad(hisq_ctx *ctx, int n, const void *r, const void *y, double *loss, double *grad);
 /* Train on n_pairs pairs (device complex128 [n_pairs][3][V/2] each) with Adam (Kingma and Ba:
  * lr, beta1 0.9, beta2 0.999, eps 1e-8, on the real and imaginary parts of the parameters as

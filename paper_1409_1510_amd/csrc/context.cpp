@@ -24,11 +24,19 @@ int set_err(hisq_ctx *ctx, int code, const char *fmt, ...) {
 bool prec_valid(int prec) { return prec == HISQ_F64 || prec == HISQ_F32 || prec == HISQ_F16; }
 size_t cplx_bytes(int prec) { return prec == HISQ_F64 ? 16 : 8; }
 
+void nn_free_state(hisq_ctx *ctx);
+bool nn_release_spare(hisq_ctx *ctx);
+
 int dev_alloc(hisq_ctx *ctx, void **p, size_t bytes, const char *what) {
-  hipError_t e = hipMalloc(p, bytes);
+  hipError_t e;
+  do {
+    *p = nullptr;
+    const bool over = ctx->dev_limit && ctx->dev_bytes + bytes > ctx->dev_limit;
+    e = over ? hipErrorOutOfMemory : hipMalloc(p, bytes);
+    if (e != hipSuccess) (void)hipGetLastError();
+  } while (e != hipSuccess && nn_release_spare(ctx));
   if (e != hipSuccess) {
     *p = nullptr;
-    (void)hipGetLastError();
     return set_err(ctx, HISQ_ERR_OOM, "%s: device allocation of %zu bytes failed: %s", what, bytes,
                    hipGetErrorString(e));
   }
@@ -86,8 +94,6 @@ static void free_links(hisq_ctx *ctx) {
   }
   ctx->links_loaded = false;
 }
-
-void nn_free_state(hisq_ctx *ctx);
 
 extern "C" {
 
@@ -148,6 +154,12 @@ int hisq_destroy(hisq_ctx *ctx) {
   if (ctx->pinned) (void)hipHostFree(ctx->pinned);
   nn_free_state(ctx);
   delete ctx;
+  return HISQ_OK;
+}
+
+int hisq_set_memory_limit(hisq_ctx *ctx, size_t bytes) {
+  if (!ctx) return HISQ_ERR_ARG;
+  ctx->dev_limit = bytes;
   return HISQ_OK;
 }
 

@@ -101,6 +101,7 @@ struct hisq_ctx {
   void *scratch_dev = nullptr;       // device address of the library's static scratch array
   size_t dev_bytes = 0;              // device memory the context holds now (dev_alloc / dev_free)
   size_t dev_peak = 0;               // largest dev_bytes since the last reset (a solve resets it)
+  size_t dev_limit = 0;              // most dev_bytes may be (0: no limit)
 };
 
 int set_err(hisq_ctx *ctx, int code, const char *fmt, ...);
@@ -126,7 +127,8 @@ int set_err(hisq_ctx *ctx, int code, const char *fmt, ...);
   } while (0)
 
 // Every device allocation of the context goes through these two, which keep dev_bytes and its
-// running peak dev_peak (links, workspace slots, tuning scratch, network state).
+// running peak dev_peak (links, workspace slots, tuning scratch, network state).  An allocation that
+// fails, or would pass dev_limit, is tried again once nn_release_spare has given memory back.
 int dev_alloc(hisq_ctx *ctx, void **p, size_t bytes, const char *what);
 void dev_free(hisq_ctx *ctx, void *p, size_t bytes);
 

@@ -123,6 +123,7 @@ def _load():
                                 ctypes.POINTER(hisq_cg_stats)]),
     }
     optional = {
+        "hisq_set_memory_limit": (cint, [vp, ctypes.c_size_t]),
         "hisq_nn_init": (cint, [vp, cint, cint, ctypes.c_ulonglong]),
         "hisq_nn_get_params": (cint, [vp, dp, cint]),
         "hisq_nn_set_params": (cint, [vp, dp, cint]),
@@ -210,6 +211,11 @@ def hisq_last_error(ctx) -> str:
 
 def hisq_set_stream(ctx, stream=None) -> None:
     _check(ctx, _lib.hisq_set_stream(ctx, _stream_ptr(stream)))
+
+
+def hisq_set_memory_limit(ctx, limit: int) -> None:
+    """Bytes of device memory the context may hold at once (0: no limit)."""
+    _check(ctx, _lib.hisq_set_memory_limit(ctx, int(limit)))
 
 
 def hisq_load_links(ctx, fat, naik, copies: int = HISQ_LINKS_ALL, naik_recon: int = 18) -> None:
