@@ -316,3 +316,47 @@ def test_matrix_core_stencil_against_the_general_kernels(dims, n, form):
     (l0, g0), (l1, g1) = got
     assert abs(l0 - l1) <= 1e-3 * abs(l1)
     assert np.linalg.norm(g0 - g1) <= 1e-3 * np.linalg.norm(g1)
+
+
+def _samples_per_wave(dims, n):
+    """Samples a wave of the matrix-core stencil takes (about 8192 waves' worth of 16-site groups);
+    from 4 on the plain stencil and its adjoint use it too, below that only the form with the weight
+    gradient does."""
+    groups = int(np.prod(dims)) // 16
+    return -(-n // min(-(-8192 // groups), n))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dims,n,spw", [((16, 16, 16, 8), 14, 4), ((24, 16, 16, 16), 9, 5), ((36, 18, 22, 10), 5, 5),
+                                        ((16, 16, 8, 8), 17, 3)])
+@pytest.mark.parametrize("form", [hisq.HISQ_NN_FORM_DIRECT, hisq.HISQ_NN_FORM_GRAM])
+def test_matrix_core_stencil_with_several_samples_per_wave(dims, n, spw, form):
+    """As above at sizes where a wave takes several samples: a last sample group of 2 of 4, of 4 of 5
+    and of all 5, 16-site groups that do not divide by the 8 XCDs (8910), and 3 samples, where
+    the plain stencil and its adjoint stay with the general kernel.  Links are random FP16 numbers
+    of the size of an SU(3) matrix's entries; the bound is that of the test above, for its reasons."""
+    assert _samples_per_wave(dims, n) == spw
+    lib = hisq.library()
+    vh = int(np.prod(dims)) // 2
+    g = torch.Generator(device=DEV)
+    g.manual_seed(8)
+    links = torch.view_as_complex((0.4 * torch.randn(2 * vh, 4, 3, 3, 2, generator=g, device=DEV)).half().double())
+    r = torch.randn(n, 3, vh, generator=g, dtype=torch.complex128, device=DEV)
+    y = torch.randn(n, 3, vh, generator=g, dtype=torch.complex128, device=DEV)
+    torch.cuda.synchronize()
+    got = []
+    for copies in (hisq.HISQ_LINKS_F16, hisq.HISQ_LINKS_F32):
+        lat = hisq.Lattice(dims, 0)
+        lat.load_links(links, links, copies)
+        assert lib.hisq_nn_init(lat.ctx, 3, 8, 7) == 0
+        assert lib.hisq_nn_set_form(lat.ctx, form) == 0
+        nreal = 2 * lib.hisq_nn_num_params(lat.ctx)
+        loss, grad = ctypes.c_double(), (ctypes.c_double * nreal)()
+        assert lib.hisq_nn_loss_grad(lat.ctx, n, hisq._ptr(r), hisq._ptr(y), ctypes.byref(loss), grad) == 0
+        got.append((loss.value, np.array(grad[:])))
+        lat.close()
+    (l0, g0), (l1, g1) = got
+    print(f"{dims} n {n} form {form}: loss {abs(l0 - l1) / abs(l1):.2e}, "
+          f"gradient {np.linalg.norm(g0 - g1) / np.linalg.norm(g1):.2e}")
+    assert abs(l0 - l1) <= 1e-3 * abs(l1)
+    assert np.linalg.norm(g0 - g1) <= 1e-3 * np.linalg.norm(g1)
