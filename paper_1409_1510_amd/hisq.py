@@ -171,9 +171,13 @@ def _check(ctx, rc: int) -> int:
 def _stream_ptr(stream):
     if stream is None:
         # the handle itself, without building a torch.cuda.Stream around it: this runs on every call
-        # (3.2 us of the 17 us that an 8^4 M takes on the host with the Stream object)
+        # (3.2 us of the 17 us that an 8^4 M takes on the host with the Stream object).  The call is a
+        # private one of torch: without it, the Stream object's handle
         import torch
-        return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        if raw is None:
+            return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+        return ctypes.c_void_p(raw(torch.cuda.current_device()))
     if isinstance(stream, int):
         return ctypes.c_void_p(stream)
     return ctypes.c_void_p(stream.cuda_stream)
