@@ -97,6 +97,32 @@ def shipped_launch(hisq, dims, prec, recon, n, fused):
     return None
 
 
+def dslash_kernel_name(cfg, dims, n, f64=False, recon=18):
+    """The kernel a launch configuration runs (the rules of launch_t and launch_lds in
+    csrc/dslash_kernel.hpp)."""
+    rt, spb, _, lds = tuple(cfg)[:4]
+    if lds == 0:
+        blocks = -(-(dims[0] * dims[1] * dims[2] * dims[3] // 2) // 64) * n
+        rows = rt == 1 and spb == 64 and recon == 18 and blocks <= (512 if f64 else 1024)
+        return "k_dslash_rows" if rows else "k_dslash"
+    if spb == 32:
+        return "k_dslash_lds32"
+    if lds >= 4:
+        return "k_dslash_mu"
+    pair = rt <= 2 if f64 else rt >= 2 and dims[0] % 4 == 0
+    return "k_dslash_pair" if pair else "k_dslash_lds"
+
+
+def counter_profile(path, kernel, cfg):
+    """path (from the repository's root) if it is a counter summary of this kernel in this launch
+    configuration, else None."""
+    if not os.path.exists(os.path.join(ROOT, path)):
+        return None
+    head = open(os.path.join(ROOT, path)).read().split("\n\n")[0]
+    taken = f"dslash::{kernel}<" in head and f"launch_config: {tuple(cfg)}\n" in head
+    return path if taken else None
+
+
 def measured_traffic(config_tuple):
     """HBM bytes per launch from the committed rocprofv3 counter summary (FETCH_SIZE and
     WRITE_SIZE, each scaled by the same counter's reading for a copy kernel of known size), if the
@@ -803,8 +829,7 @@ def main():
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                      "traffic": measured_traffic(launch_cfg),
-                     "kernel": (("k_dslash_pair" if launch_cfg[0] >= 2 and launch_cfg[1] == 64 and launch_cfg[3] <= 3
-                                 else "k_dslash_lds") if launch_cfg[3] else "k_dslash") + " (half Dslash, FP32)",
+                     "kernel": dslash_kernel_name(launch_cfg, dims, n) + " (half Dslash, FP32)",
                      "launch_config": {"rhs_per_thread": launch_cfg[0], "sites_per_block": launch_cfg[1],
                                        "nontemporal_links": launch_cfg[2], "lds_links": launch_cfg[3],
                                        "xcd_map": launch_cfg[4]},
@@ -857,11 +882,12 @@ def main():
                if e["lattice"] == "64x64x64x16" and e["prec"] == "f32" and e["n"] == 16]
         if big:
             e = big[0]
+            kernel = dslash_kernel_name(e["launch"], (64, 64, 64, 16), e["n"])
             result["roofline_64x64x64x16"] = {
                 "bound": "hbm", "achieved": e["compulsory_GBps"], "peak": 8000.0, "unit": "GB/s",
                 "frac": round(e["compulsory_GBps"] / 8000.0, 4),
-                "kernel": "k_dslash_pair (half Dslash, FP32, 16 rhs)", "launch": e["launch"],
-                "counters": "profiles/k_dslash_f32_n16_64x64x64x16.txt (k_dslash_lds)"}
+                "kernel": kernel + " (half Dslash, FP32, 16 rhs)", "launch": e["launch"],
+                "counters": counter_profile("profiles/k_dslash_f32_n16_64x64x64x16.txt", kernel, e["launch"])}
 
     if not args.no_cg:
         c2 = synth.WORKLOADS["c2"]

@@ -49,6 +49,32 @@ def test_sweep_cases_cover_every_naik_format():
     assert len({name for _, _, name in cases}) == len(cases)
 
 
+def test_kernel_named_from_the_launch():
+    """One configuration per branch of the launch rules, and the limits of the row form."""
+    d, odd = (32, 32, 32, 8), (30, 32, 32, 8)
+    for cfg, dims, n, f64, recon, name in [
+            ((2, 64, 1, 2, 3), d, 16, False, 18, "k_dslash_pair"), ((2, 64, 1, 2, 0), odd, 16, False, 18, "k_dslash_lds"),
+            ((1, 64, 1, 2, 0), d, 16, False, 18, "k_dslash_lds"), ((4, 64, 1, 1, 0), d, 16, False, 14, "k_dslash_pair"),
+            ((1, 64, 1, 2, 0), odd, 8, True, 18, "k_dslash_pair"), ((4, 64, 1, 2, 0), d, 8, True, 18, "k_dslash_lds"),
+            ((1, 32, 1, 2, 0), d, 8, True, 18, "k_dslash_lds32"), ((1, 64, 0, 5, 0), d, 8, False, 18, "k_dslash_mu"),
+            ((2, 256, 0, 0, 0), d, 8, False, 18, "k_dslash"), ((1, 256, 0, 0, 0), (8, 8, 8, 8), 1, False, 18, "k_dslash"),
+            ((1, 64, 0, 0, 0), (8, 8, 8, 8), 32, False, 18, "k_dslash_rows"),
+            ((1, 64, 0, 0, 0), (8, 8, 8, 8), 33, False, 18, "k_dslash"),
+            ((1, 64, 0, 0, 0), (8, 8, 8, 8), 16, True, 18, "k_dslash_rows"),
+            ((1, 64, 0, 0, 0), (8, 8, 8, 8), 17, True, 18, "k_dslash"),
+            ((1, 64, 0, 0, 0), (8, 8, 8, 8), 1, False, 14, "k_dslash")]:
+        assert bench.dslash_kernel_name(cfg, dims, n, f64, recon) == name, (cfg, dims, n)
+
+
+def test_counters_only_of_the_kernel_that_ran():
+    path = os.path.relpath(bench.PROFILE_SUMMARY, ROOT)
+    cfg = bench.shipped_launch(_Hisq, (32, 32, 32, 8), 1, 18, 16, 0)
+    assert bench.counter_profile(path, bench.dslash_kernel_name(cfg, (32, 32, 32, 8), 16), cfg) == path
+    assert bench.counter_profile(path, "k_dslash_mu", cfg) is None
+    assert bench.counter_profile(path, "k_dslash_pair", (1,) + tuple(cfg[1:])) is None
+    assert bench.counter_profile("profiles/none.txt", "k_dslash_pair", cfg) is None
+
+
 def test_more_than_one_gpu_is_refused():
     """bench.py measures one GPU: --gpus N > 1 exits with a message before touching a device."""
     import subprocess
