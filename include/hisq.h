@@ -152,14 +152,19 @@ int hisq_dot_mrhs_noalloc(hisq_ctx *ctx, int prec, int n, const void *a, const v
 typedef struct {
   int rhs_per_thread;    /* register tile: 1, 2, 4, 8 or 16 (FP64 and the fused-M form: <= 8)  */
   int sites_per_block;   /* 256: one rhs tile per 256-thread workgroup; 64: the 4 waves of a     */
-                         /*      workgroup take 4 rhs tiles of the same 64 sites; 32: the       */
+                         /*      workgroup take 4 rhs tiles of the same 64 sites, or, with      */
+                         /*      rhs_per_thread 1, 18-real links and at most 512 (FP64) or 1024 */
+                         /*      blocks of 64 sites times n, three waves take a row of the      */
+                         /*      product each for one rhs; 32: the                              */
                          /*      32-site LDS form (lds_links 1 or 2 = 4 or 8 waves, rhs_per_    */
                          /*      thread 1 or 2, the two halves of a wave on different rhs), for */
                          /*      the plain half Dslash only: hisq_set_launch leaves the fused-M */
                          /*      configuration unchanged for it                                 */
   int nontemporal_links; /* 1: link loads carry the non-temporal cache hint                     */
   int lds_links;         /* 1, 2, 3: a workgroup of 64 sites x 4, 8, 16 waves stages its sites'  */
-                         /*    links in LDS and its waves loop over the rhs tiles (requires      */
+                         /*    links in LDS and its waves loop over the rhs tiles, with 16-byte  */
+                         /*    gathers issued ahead where rhs_per_thread is 1 or 2 (FP64) or     */
+                         /*    above 1 with Lx divisible by 4 (FP32, FP16 links) (requires       */
                          /*    sites_per_block = 64, rhs_per_thread <= 4 (<= 2 for 16 waves);    */
                          /*    FP64 links take a CU's LDS alone, FP32/FP16 links fit twice);     */
                          /* 4, 5, 6: the same with the links staged one direction at a time in  */

@@ -33,8 +33,10 @@ FLAGS = [
 # per-unit scheduler: the FP64 Dslash instances are scheduled for instruction-level parallelism
 # (LLVM's max-ilp strategy), measured 1.7-2.4 % faster FP64 LDS launches at 8 and 16 rhs
 # (32^3 x 8: 94.5 us against 96.1, fused M 98.6 against 101.0, 16 rhs 132 against 135).  The FP32 and FP16-link
-# units keep the default strategy, under which their 16-rhs launches are 8-10 % faster than with
-# max-ilp.  Scheduling only orders instructions: every output stays bit-identical.
+# units keep the default strategy: default against max-ilp, 32^3 x 8: both half Dslash in FP32 on 16 rhs
+# 147.9 against 153.0 us, M with FP16 links on 8 rhs 81.4 against 83.1; 48^3 x 12, M in FP32 on 16 rhs 892
+# against 868 (max-ilp ahead); 64^3 x 16, FP16 links, 32 rhs 4171 against 4151.  Scheduling only orders
+# instructions: every output stays bit-identical.
 EXTRA_FLAGS = {"dslash_f64.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"]}
 
 

@@ -1094,8 +1094,9 @@ __device__ inline void site_value(const v4u_t &x, int, double &re, double &im) {
 // 16).  What bounds the one-site form is the rate at which a CU's vector memory path takes load
 // instructions: a wave's 8-byte loads move 32 bytes per clock, its 16-byte loads 62 (measured on
 // L1-resident data), so a tile's gathers alone cost ~41 us of the 76 us launch at 32^3 x 8 with
-// 16 rhs (FP32).  Here every gather, link staging load and store is 16 bytes wide: 66 us; 58 us of
-// that remain without any arithmetic or link reads, 344 MB past L2 at 5.9 TB/s.
+// 16 rhs (FP32).  Here every gather, link staging load and store is 16 bytes wide: 66 us by the tuner's
+// clock (58 us of that remain without any arithmetic or link reads), 69 us in a kernel trace, where
+// 355 MB, 1.41 times the compulsory bytes, go past L2 at 5.2 TB/s.
 //   * y, z and t neighbours of a pair are a pair; the eight x neighbours of a pair are all among
 //     the pair itself and the pairs before and after it in its row (three loads, not four), picked
 //     by the parity of the row.

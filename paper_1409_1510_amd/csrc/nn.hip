@@ -246,10 +246,15 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // lane's channel, contraction over (re, im) of the neighbour's colours).  An FP16 link entry (11
 // significant bits) is the exact sum of two BF16 numbers (8 bits each) and activations are BF16, so
 // every product is exact and the accumulation FP32, as with FP32 arithmetic on the FP16 links: three
-// instructions contract (high u0, u1), (high u2, low u2), (low u0, u1).  What bounds the one-thread-
-// per-site kernel is the FP32 arithmetic of the products (1152 of ~1600 cycles per hop and 64 sites);
-// here they take 384 on the matrix cores beside the rest.  The split links of a site (48 registers)
-// serve all samples of the wave; the gradient sums stay in FP64 registers over all sites of a wave.
+// instructions contract (high u0, u1), (high u2, low u2), (low u0, u1).  (An infinite activation times
+// a low part of zero is NaN where the FP32 product was infinite: sums that overflowed stay non-finite,
+// and finite ones are finite for the same inputs.)  What bounds the one-thread-per-site kernel is the
+// FP32 arithmetic of the products (1152 of ~1600 cycles per hop and 64 sites); here they take 384 on the
+// matrix cores beside the rest.  The split links of a site (48 registers) serve all samples of the
+// wave; the gradient sums stay in FP64 registers over all sites of a wave.  What bounds it now is the
+// traffic past L2: at 32^3 x 8 with 16 samples a plain pass moves 2.3 GB, 2.6 times the compulsory
+// bytes, at 5.3 TB/s; the form with the gradient 2.9 GB at 4.5 TB/s, its waves (two a SIMD) issuing VALU
+// instructions for a third of their time.
 // Figures: at stencil_mfma below.
 struct StencilArgs {
   Geometry g;
@@ -1246,7 +1251,9 @@ int stencil_spw(const hisq_ctx *ctx, int batch) {
 // Measured at 32^3 x 8 with 16 samples: 0.43 ms per launch with all 16 samples per wave, 0.45 with 8,
 // 0.48 with 4 and 0.56 with 2, against 0.54 of k_nn_stencil, so the plain stencil takes it from 4 on;
 // with the weight gradient 0.65, 0.71, 0.80 and 0.99 ms against 1.93 of k_nn_stencil and
-// k_nn_stencil_wgrad, so that form always does.  (Two samples per wave in 16-byte loads, four channels
+// k_nn_stencil_wgrad, so that form always does, also with a single sample per wave (a whole gradient, 4
+// layers, one pair, direct form, general kernels -> this: 4^4 774 -> 264 us, 8^4 791 -> 266, 16^4 928 -> 460,
+// 32^3 x 8 1364 -> 861, 48^3 x 12 4486 -> 3636).  (Two samples per wave in 16-byte loads, four channels
 // per lane, and a z-outermost site order: 0.43-0.45 ms; three or four waves per SIMD, with spills:
 // 0.44-0.53 ms.)
 bool stencil_mfma(const hisq_ctx *ctx, int prec, int batch, bool wgrad) {
