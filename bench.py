@@ -97,19 +97,32 @@ def shipped_launch(hisq, dims, prec, recon, n, fused):
     return None
 
 
-def dslash_kernel_name(cfg, dims, n, f64=False, recon=18):
-    """The kernel a launch configuration runs (the rules of launch_t and launch_lds in
-    csrc/dslash_kernel.hpp)."""
+def dslash_kernel_name(cfg, dims, n, elem=8, recon=18, fused=False):
+    """The kernel a launch configuration runs (the rules of launch_t, launch_lds and pair_form_pays in
+    csrc/dslash_kernel.hpp); elem: bytes of a stored link entry (16 FP64, 8 FP32, 4 FP16)."""
     rt, spb, _, lds = tuple(cfg)[:4]
+    blocks = -(-(dims[0] * dims[1] * dims[2] * dims[3] // 2) // 64)
     if lds == 0:
-        blocks = -(-(dims[0] * dims[1] * dims[2] * dims[3] // 2) // 64) * n
-        rows = rt == 1 and spb == 64 and recon == 18 and blocks <= (512 if f64 else 1024)
+        rows = rt == 1 and spb == 64 and recon == 18 and blocks * n <= (512 if elem == 16 else 1024)
         return "k_dslash_rows" if rows else "k_dslash"
     if spb == 32:
         return "k_dslash_lds32"
     if lds >= 4:
         return "k_dslash_mu"
-    pair = rt <= 2 if f64 else rt >= 2 and dims[0] % 4 == 0
+    tiles, wide = -(-n // rt), rt > 2
+    if elem == 16:
+        pair = rt <= 2 and not (rt == 1 and lds == 2 and blocks < 768)
+    elif rt < 2 or dims[0] % 4:
+        pair = False
+    elif lds == 1 and wide:
+        pair = elem == 8 or tiles >= 3 or blocks <= 256
+    elif lds == 1:
+        pair = tiles >= 2 and not (recon == 9 if elem == 4 else recon in (13, 14) and not fused and blocks < 1536)
+    elif lds == 2:
+        every = recon == 9 or (elem == 4 and (wide or recon != 18))
+        pair = tiles >= (8 if every else (2 if wide else 3)) or (wide and blocks <= 256)
+    else:
+        pair = tiles >= 16 or blocks <= 256
     return "k_dslash_pair" if pair else "k_dslash_lds"
 
 

@@ -1790,17 +1790,52 @@ void launch_t(const Args &a, dim3 grid, hipStream_t st) {
   k_dslash<Real, LT, RT, NR, EPI, SPB, NT><<<grid, 256, 0, st>>>(a);
 }
 
+// Whether the pair form runs a whole-site LDS launch (elem: bytes of a stored link entry, 16, 8 or 4;
+// nr: reals of a Naik link; rt rhs per thread; wpb waves; ntiles rhs tiles; nsblk 64-site blocks), or the
+// one-site form.  The pair form looks ahead where the one-site form has more waves in flight, so it
+// pays where its waves have work; a configuration that is forced or was stored for the one-site form
+// must not lose by it elsewhere.  Measured on 1520 launches (8 lattices of 256 to 10368 blocks, 2 to 32
+// rhs, all formats), one-site time over pair time, geometric mean and range, where the rule takes
+// the pair form | where it does not:
+//   FP64         1.14 (1.01-1.43), 8 waves 1.10 (0.98-1.32) | one rhs in 8 waves on few blocks 0.97 (0.84-1.07)
+//   FP32  4 waves 1.16 (0.92-1.55) | 0.95 (0.81-1.02): one tile, or r14 and r13 plain on small lattices
+//         8 waves 1.11 (0.78-1.58) | 0.94 (0.70-1.25): idle waves, the 9-real format that reads its
+//                                    rebuilt links from LDS in full
+//        16 waves 1.08 (0.98-1.22) | 0.86 (0.65-1.09): idle waves
+//   FP16  4 waves 1.10 (0.94-1.25) | 1.01 (0.86-1.26): one tile, 9 reals, four rhs on two tiles
+//         8 waves 1.10 (0.93-1.55) | 0.92 (0.67-1.26): idle waves, formats that rebuild, four rhs
+//        16 waves 1.07 (0.92-1.21) | 0.79 (0.61-0.98): idle waves
+// With at most one workgroup per CU the one-site form has no further waves to offer.  (The 0.78 is 16^4
+// with 32 rhs in FP32; the fastest launch of each of the 266 cases stays within 2 % of both forms' best.)
+constexpr int kCUs = 256;
+__host__ __device__ constexpr bool pair_form_pays(int elem, int nr, int rt, int wpb, bool epi, int ntiles, int nsblk) {
+  if (elem == 16) return rt <= 2 && !(rt == 1 && wpb == 8 && nsblk < 3 * kCUs);
+  if (rt < 2) return false;
+  const bool f16 = elem == 4;
+  if (wpb == 4) {
+    if (rt > 2) return !f16 || ntiles >= 3 || nsblk <= kCUs;
+    if (f16 && nr == 9) return false;
+    if (!f16 && (nr == 14 || nr == 13) && !epi && nsblk < 6 * kCUs) return false;
+    return ntiles >= 2;
+  }
+  if (wpb == 8) {
+    const bool every = nr == 9 || (f16 && (rt > 2 || nr != 18));  // needs a tile for every wave
+    return ntiles >= (every ? 8 : (rt > 2 ? 2 : 3)) || (rt > 2 && nsblk <= kCUs);
+  }
+  return ntiles >= 16 || nsblk <= kCUs;
+}
+
 template <typename Real, typename LT, int RT, int NR, bool EPI, int WPB, bool NT>
 void launch_lds(const Args &a, dim3 grid, hipStream_t st) {
   constexpr bool f64 = sizeof(Real) == 8;
-  if constexpr (f64 ? RT <= 2 : RT >= 2) {
-    if (f64 || a.g.lx % 4 == 0) {
+  if constexpr (f64 ? RT <= 2 : RT >= 2 && !(sizeof(LT) == 4 && NR == 9 && RT == 2 && WPB == 4)) {
+    if ((f64 || a.g.lx % 4 == 0) && pair_form_pays(sizeof(LT), NR, RT, WPB, EPI, a.ntiles, a.nsblk)) {
       k_dslash_pair<Real, LT, f64 ? RT : RT / 2, NR, EPI, WPB, NT>
           <<<grid, 64 * WPB, lds_nbr_offset<Real, LT, NR>() + nbr_table_pair_bytes<Real>(), st>>>(a);
       return;
     }
   }
-  if constexpr (!f64 || RT > 2) {
+  if constexpr (!f64 || RT > 2 || (RT == 1 && WPB == 8)) {
     constexpr size_t lds = lds_nbr_offset<Real, LT, NR>() + kNbrTableBytes;
     k_dslash_lds<Real, LT, RT, NR, EPI, WPB, NT><<<grid, 64 * WPB, lds, st>>>(a);
   }

@@ -51,19 +51,19 @@ def test_sweep_cases_cover_every_naik_format():
 
 def test_kernel_named_from_the_launch():
     """One configuration per branch of the launch rules, and the limits of the row form."""
-    d, odd = (32, 32, 32, 8), (30, 32, 32, 8)
-    for cfg, dims, n, f64, recon, name in [
-            ((2, 64, 1, 2, 3), d, 16, False, 18, "k_dslash_pair"), ((2, 64, 1, 2, 0), odd, 16, False, 18, "k_dslash_lds"),
-            ((1, 64, 1, 2, 0), d, 16, False, 18, "k_dslash_lds"), ((4, 64, 1, 1, 0), d, 16, False, 14, "k_dslash_pair"),
-            ((1, 64, 1, 2, 0), odd, 8, True, 18, "k_dslash_pair"), ((4, 64, 1, 2, 0), d, 8, True, 18, "k_dslash_lds"),
-            ((1, 32, 1, 2, 0), d, 8, True, 18, "k_dslash_lds32"), ((1, 64, 0, 5, 0), d, 8, False, 18, "k_dslash_mu"),
-            ((2, 256, 0, 0, 0), d, 8, False, 18, "k_dslash"), ((1, 256, 0, 0, 0), (8, 8, 8, 8), 1, False, 18, "k_dslash"),
-            ((1, 64, 0, 0, 0), (8, 8, 8, 8), 32, False, 18, "k_dslash_rows"),
-            ((1, 64, 0, 0, 0), (8, 8, 8, 8), 33, False, 18, "k_dslash"),
-            ((1, 64, 0, 0, 0), (8, 8, 8, 8), 16, True, 18, "k_dslash_rows"),
-            ((1, 64, 0, 0, 0), (8, 8, 8, 8), 17, True, 18, "k_dslash"),
-            ((1, 64, 0, 0, 0), (8, 8, 8, 8), 1, False, 14, "k_dslash")]:
-        assert bench.dslash_kernel_name(cfg, dims, n, f64, recon) == name, (cfg, dims, n)
+    d, odd, small = (32, 32, 32, 8), (30, 32, 32, 8), (8, 8, 8, 8)
+    for cfg, dims, n, elem, recon, name in [
+            ((2, 64, 1, 2, 3), d, 16, 8, 18, "k_dslash_pair"), ((2, 64, 1, 2, 0), odd, 16, 8, 18, "k_dslash_lds"),
+            ((1, 64, 1, 2, 0), d, 16, 8, 18, "k_dslash_lds"), ((4, 64, 1, 1, 0), d, 16, 8, 14, "k_dslash_pair"),
+            ((2, 64, 1, 3, 0), d, 16, 8, 18, "k_dslash_lds"), ((2, 64, 1, 3, 0), d, 31, 8, 18, "k_dslash_pair"),
+            ((1, 64, 1, 2, 0), odd, 8, 16, 18, "k_dslash_pair"), ((4, 64, 1, 2, 0), d, 8, 16, 18, "k_dslash_lds"),
+            ((1, 64, 1, 2, 0), (16, 16, 16, 16), 8, 16, 18, "k_dslash_lds"),
+            ((1, 32, 1, 2, 0), d, 8, 16, 18, "k_dslash_lds32"), ((1, 64, 0, 5, 0), d, 8, 8, 18, "k_dslash_mu"),
+            ((2, 256, 0, 0, 0), d, 8, 8, 18, "k_dslash"), ((1, 256, 0, 0, 0), small, 1, 8, 18, "k_dslash"),
+            ((1, 64, 0, 0, 0), small, 32, 8, 18, "k_dslash_rows"), ((1, 64, 0, 0, 0), small, 33, 8, 18, "k_dslash"),
+            ((1, 64, 0, 0, 0), small, 16, 16, 18, "k_dslash_rows"), ((1, 64, 0, 0, 0), small, 17, 16, 18, "k_dslash"),
+            ((1, 64, 0, 0, 0), small, 1, 8, 14, "k_dslash")]:
+        assert bench.dslash_kernel_name(cfg, dims, n, elem, recon) == name, (cfg, dims, n)
 
 
 def test_counters_only_of_the_kernel_that_ran():
